@@ -21,7 +21,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libdn.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["conv.hip", "aux.hip", "backward.hip", "detect.hip", "jacobi.hip", "runtime.cpp"]
+SOURCES = ["conv.hip", "conv_pipe.hip", "aux.hip", "backward.hip", "detect.hip", "jacobi.hip", "runtime.cpp"]
 HOST_SOURCES = ["cpu_layers.cpp", "ga.cpp"]
 ARCH = "gfx950"
 
@@ -33,7 +33,7 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found (ROCm is required to build libdn.so)")
 
 
-COMMON = ["-O3", "-fPIC", "-std=c++17", "--offload-arch=" + ARCH,
+COMMON = ["-O3", "-fPIC", "-std=c++20", "--offload-arch=" + ARCH,
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wall", "-Wno-unused-function", "-I", INCLUDE, "-I", CSRC]
 

@@ -101,6 +101,12 @@ constexpr int HALO2_TILE = 101;
 bool halo2_ok(int dt, const ConvArgs &a);
 hipError_t launch_conv_halo2(int dt, const ConvArgs &a, hipStream_t s);
 
+// The pipelined GEMM kernel (conv_pipe.hip): tiles PIPE_TILE .. + PIPE_TILES - 1
+// of the table, for convs that pipe_ok().
+constexpr int PIPE_TILE = 48, PIPE_TILES = 10;
+bool pipe_ok(int dt, const ConvArgs &a);
+hipError_t launch_conv_pipe(int dt, int i, const ConvArgs &a, hipStream_t s);
+
 struct TileCfg { int bm, bn, wm, wn, mf; };  // mf: MFMA block side for BF16 (0 = 16)
 
 int tile_count();

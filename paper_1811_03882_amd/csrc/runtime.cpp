@@ -236,6 +236,71 @@ static void heuristic_tile(int M, int N, int K, int *tile, int *splits)
     *splits = s;
 }
 
+// Tile of the pipelined kernel (convs that pipe_ok()) for an M x N output,
+// `nkt` K-tiles in all and `splits` of them side by side.  A CU's time per
+// K-tile is about cost x (workgroups it runs), but never less than what one
+// workgroup takes alone (alone), which barriers and LDS latency set; each
+// round adds its prologue and epilogue (round).  cost / alone / round: fitted
+// to BF16 timings on MI355X (microseconds per K-tile: 13x13x1024 -> 1024 and
+// 13x13x512 -> 1024 at batch 64 and 16, 16x16x256 -> 512 at batch 16,
+// 52x52x64 -> 128 and its gradient); FP8 measured within 10 % of the same
+// figures.  FP32 is bound by its matrix rate: 64 values per clock and SIMD.
+struct PipeCost { float cost, alone, round; int per_cu; };
+static const PipeCost kPipeCost[PIPE_TILES] = {
+    {1.33f, 1.33f, 6.0f, 1},   // 256x256
+    {1.22f, 1.22f, 6.0f, 1},   // 192x256
+    {0.50f, 0.60f, 3.0f, 2},   // 128x128
+    {0.44f, 0.58f, 3.0f, 2},   // 96x128
+    {0.30f, 0.47f, 3.0f, 2},   // 64x128
+    {0.30f, 0.47f, 3.0f, 3},   // 128x64
+    {0.26f, 0.45f, 3.0f, 3},   // 96x64
+    {0.17f, 0.42f, 3.0f, 3},   // 64x64
+    {0.115f, 0.42f, 3.0f, 4},  // 64x32
+    {0.62f, 0.72f, 4.0f, 2},   // 192x128
+};
+
+static bool finish_in_kernel(int tile, int splits);
+
+// Microseconds the pipelined tile is expected to take; in_net: split convs may
+// finish in the GEMM launch.
+static float pipe_time(int dt, int i, int M, int N, int nkt, int splits, bool in_net)
+{
+    const int CUS = 256;
+    const TileCfg t = tile_cfg(PIPE_TILE + i);
+    PipeCost c = kPipeCost[i];
+    if (dt == F32) {
+        c.cost = (float)t.bm * t.bn / 256.0f * 64.0f / 2100.0f / 1.0f;
+        c.alone = std::max(c.alone, c.cost);
+    }
+    if (dt == FP8 && i == PIPE_TILES - 1) c = {0.95f, 0.95f, 4.0f, 1};  // more registers per wave
+    const float kt = (float)((nkt + splits - 1) / splits);
+    const double wgs = (double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
+    // workgroups of the busiest CU: whole ones while few, the mean once
+    // enough rounds even out
+    const double mean = wgs / CUS;
+    const double n = mean > 3.0 * c.per_cu ? mean : std::ceil(mean);
+    const double full = std::floor(n / c.per_cu), rest = n - full * c.per_cu;
+    double us = full * (kt * std::max(c.alone, c.cost * c.per_cu) + c.round);
+    if (rest > 0) us += kt * std::max((double)c.alone, c.cost * rest) + c.round;
+    if (splits > 1) {
+        const double mb = 2.0 * splits * M * N * 4.0 / 1e6;
+        us += in_net && finish_in_kernel(PIPE_TILE + i, splits) ? 2.0 + mb / 3.0 : 5.0 + mb / 3.0;
+    }
+    return (float)us;
+}
+
+static int pipe_tile(int dt, int M, int N, int nkt, int splits, bool in_net, float *us = nullptr)
+{
+    int best = 0;
+    float bt = 1e30f;
+    for (int i = 0; i < PIPE_TILES; ++i) {
+        const float v = pipe_time(dt, i, M, N, nkt, splits, in_net);
+        if (v < bt) { bt = v; best = i; }
+    }
+    if (us) *us = bt;
+    return PIPE_TILE + best;
+}
+
 // Tune-cache signature of a forward conv; batch-invariant nets keep their
 // own entries (their candidates are restricted, see below).
 static std::string conv_sig(int dt, const Op &op, int batch, int R, int stride, bool inv)
@@ -346,6 +411,18 @@ static bool op_halo2_ok(const dn_net *net, int dtype, const Op &op, int k_pad)
     a.cin_p = op.cin_p; a.cout_p = op.cout_p; a.k_pad = k_pad;
     a.H = op.H; a.W = op.W; a.Ho = op.pool ? op.Ho * 2 : op.Ho; a.Wo = op.pool ? op.Wo * 2 : op.Wo;
     return halo2_ok(dtype, a);
+}
+
+// Can this conv op run the pipelined GEMM tiles?
+static bool op_pipe_ok(const dn_net *net, int dtype, const Op &op, int batch, int k_pad)
+{
+    if (op.kind != OP_CONV || op.first) return false;
+    const dn_layer_desc &d = net->L[op.conv];
+    ConvArgs a{};
+    a.R = a.S = d.ksize; a.stride = d.stride; a.pad = d.pad;
+    a.cin_p = op.cin_p; a.cout_p = op.cout_p; a.k_pad = k_pad;
+    a.batch = batch; a.H = op.H; a.W = op.W;
+    return pipe_ok(dtype, a);
 }
 
 // pool_fuse_upto >= 0 (input-gradient pass, per-layer mode otherwise): fuse a
@@ -511,18 +588,26 @@ static dn_status make_plan(const dn_net *net, int dtype, int mode, int batch, in
         } else if (op_halo2_ok(net, dtype, op, k_pad)) {
             op.tile = HALO2_TILE;
             op.splits = 1;
-        } else if (op_halo_ok(net, dtype, op, k_pad)) {
-            op.tile = HALO_TILE;
-            op.splits = 1;
         } else {
+            // the split count, which orders each output's sum, is the same
+            // whichever tile then runs it
+            const bool halo = op_halo_ok(net, dtype, op, k_pad);
             heuristic_tile(M, op.cout_p, k_pad / bk_el(dtype), &op.tile, &op.splits);
+            if (halo) op.splits = 1;
+            if (op_pipe_ok(net, dtype, op, batch, k_pad))
+                op.tile = pipe_tile(dtype, M, op.cout_p, k_pad / bk_el(dtype), op.splits, true);
+            else if (halo)
+                op.tile = HALO_TILE;
         }
         if (inv) {
+            const bool tuned = it != net->tuned.end();
             op.splits = invariant_splits(k_pad / bk_el(dtype));
             if (!invariant_tile_ok(dtype, op.tile, op.splits)) {
                 int unused;
                 heuristic_tile(M, op.cout_p, k_pad / bk_el(dtype), &op.tile, &unused);  // 16x16-block tiles
             }
+            if (!tuned && !is_halo(op.tile) && op_pipe_ok(net, dtype, op, batch, k_pad))
+                op.tile = pipe_tile(dtype, M, op.cout_p, k_pad / bk_el(dtype), op.splits, true);
         }
         op.ws_bytes = op.splits > 1 ? align256((size_t)op.splits * M * op.cout_p * 4) : 0;
         ws = std::max(ws, op.ws_bytes);
@@ -1643,7 +1728,8 @@ extern "C" dn_status dn_autotune(dn_net *net, int batch, int h, int w, void *str
         std::vector<int> cands;
         if (op_halo_ok(net, p.dtype, op, net->cw[op.conv].k_pad)) cands.push_back(HALO_TILE);
         if (op_halo2_ok(net, p.dtype, op, net->cw[op.conv].k_pad)) cands.push_back(HALO2_TILE);
-        for (int t = 0; t < tile_count(); ++t)
+        const bool pipe = op_pipe_ok(net, p.dtype, op, batch, net->cw[op.conv].k_pad);
+        for (int t = 0; t < (pipe ? tile_count() : PIPE_TILE); ++t)
             if (tile_fits(t, op.cout_p)) cands.push_back(t);
         for (int t : cands) {
             if (rc != DN_OK) break;
@@ -1961,10 +2047,32 @@ static dn_status conv_geometry(const dn_conv_desc *d, ConvArgs *a, int *tile, in
     int t = d->tile, sp = d->splits;
     int ht, hs;
     heuristic_tile(M, cout_p, k_pad / bk_el(dt), &ht, &hs);
+    const int nkt = std::max(1, k_pad / bk_el(dt));
+    if (t < 0 && !d->input_nchw) {
+        ConvArgs g{};
+        g.batch = d->batch; g.H = d->in_h; g.W = d->in_w; g.Ho = Ho; g.Wo = Wo;
+        g.R = g.S = d->ksize; g.stride = d->stride; g.pad = d->pad; g.cin_p = cin_p; g.cout_p = cout_p; g.k_pad = k_pad;
+        if (sp <= 0 && halo2_ok(dt, g)) {
+            // small K: the persistent halo kernel reads every input pixel once
+            // (104x104x32 -> 64 + pool, batch 64, BF16: 69 us on a GEMM tile)
+            t = HALO2_TILE;
+        } else if (pipe_ok(dt, g)) {
+            // here a split costs a second launch (the workspace has no zeroed
+            // counters for the in-kernel finish): split only where that pays
+            if (sp <= 0) {
+                float best = 1e30f;
+                for (int s = 1; s <= 16 && s <= nkt; s *= 2) {
+                    float us;
+                    pipe_tile(dt, M, cout_p, nkt, s, false, &us);
+                    if (us < best) { best = us; sp = s; }
+                }
+            }
+            t = pipe_tile(dt, M, cout_p, nkt, sp, false);
+        }
+    }
     if (t < 0) t = ht;
     if (sp <= 0) sp = (d->tile < 0) ? hs : 1;
     if (t >= tile_count() && !is_halo(t)) return fail(DN_EINVAL, "tile %d out of range", t);
-    const int nkt = std::max(1, k_pad / bk_el(dt));
     if (sp > nkt) sp = nkt;
     if (d->input_nchw || is_halo(t)) sp = 1;
     if (is_halo(t)) {
@@ -2150,9 +2258,28 @@ static dn_status bwd_desc(const dn_conv_desc *f, int accumulate, dn_conv_desc *b
         b->splits = is_halo(tile) ? 1 : std::max(1, splits);
     } else if (halo2_ok(f->dtype, a)) {
         b->tile = HALO2_TILE;
-    } else if (halo_ok(f->dtype, a)) {
+    } else if (!pipe_ok(f->dtype, a) && halo_ok(f->dtype, a)) {
         b->tile = HALO_TILE;
     }
+    return DN_OK;
+}
+
+// Untuned (tile, splits) of a backward-data conv inside a net's pass: as the
+// forward plan's, the split count does not depend on the tile that runs it.
+static dn_status bwd_plan_tile(const dn_conv_desc *f, int accumulate, int *tile, int *splits)
+{
+    dn_conv_desc b;
+    int ho, wo, hz, wz;
+    STCHK(bwd_desc(f, accumulate, &b, &ho, &wo, &hz, &wz));
+    ConvArgs a;
+    STCHK(conv_geometry(&b, &a, nullptr, nullptr, nullptr, nullptr, nullptr));
+    *tile = b.tile;
+    *splits = 1;
+    if (is_halo(b.tile)) return DN_OK;
+    const int nkt = a.k_pad / bk_el(f->dtype);
+    heuristic_tile(a.M, a.cout_p, nkt, tile, splits);
+    if (halo_ok(f->dtype, a)) *splits = 1;
+    if (pipe_ok(f->dtype, a)) *tile = pipe_tile(f->dtype, a.M, a.cout_p, nkt, *splits, false);
     return DN_OK;
 }
 
@@ -2385,6 +2512,7 @@ static dn_status make_bwd_plan(const dn_net *net, int target, int batch, int h, 
         f.in_scale = f.res_scale = f.out_scale = 1.0f; f.tile = -1;
         auto it = net->tuned.find(bwd_sig(&f, b.acc[k]));
         if (it != net->tuned.end()) b.btile[k] = it->second;
+        else STCHK(bwd_plan_tile(&f, b.acc[k], &b.btile[k].first, &b.btile[k].second));
         dn_conv_desc bd;
         int ho, wo, hz, wz;
         STCHK(bwd_desc(&f, b.acc[k], &bd, &ho, &wo, &hz, &wz, b.btile[k].first, b.btile[k].second));
@@ -2639,7 +2767,8 @@ static dn_status autotune_backward(dn_net *net, int layer, int batch, int h, int
         std::vector<int> cands;
         if (op_halo_ok(net, dt, op, net->cw[op.conv].k_pad)) cands.push_back(HALO_TILE);
         if (op_halo2_ok(net, dt, op, net->cw[op.conv].k_pad)) cands.push_back(HALO2_TILE);
-        for (int t = 0; t < tile_count(); ++t)
+        const bool pipe = op_pipe_ok(net, dt, op, batch, net->cw[op.conv].k_pad);
+        for (int t = 0; t < (pipe ? tile_count() : PIPE_TILE); ++t)
             if (tile_fits(t, op.cout_p)) cands.push_back(t);
         std::vector<std::tuple<float, int, int>> timed;
         for (int t : cands) {
@@ -2678,7 +2807,7 @@ static dn_status autotune_backward(dn_net *net, int layer, int batch, int h, int
         std::vector<int> cands;
         if (halo_ok(dt, a)) cands.push_back(HALO_TILE);
         if (halo2_ok(dt, a)) cands.push_back(HALO2_TILE);
-        for (int t = 0; t < tile_count(); ++t)
+        for (int t = 0; t < (pipe_ok(dt, a) ? tile_count() : PIPE_TILE); ++t)
             if (tile_fits(t, a.cout_p)) cands.push_back(t);
         std::vector<std::tuple<float, int, int>> timed;
         for (int t : cands) {
