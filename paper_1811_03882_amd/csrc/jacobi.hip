@@ -17,6 +17,8 @@
 
 namespace dnk {
 
+// one iteration per launch (the per-iteration transfer mode, and grids too tall
+// for the tiled kernel's launch below)
 constexpr int JAC_BX = 64, JAC_BY = 4, JAC_STRIP = 8;
 
 __global__ void __launch_bounds__(JAC_BX * JAC_BY) jacobi_step(const double *__restrict__ u, double *__restrict__ v,
@@ -56,12 +58,214 @@ __global__ void __launch_bounds__(JAC_BX * JAC_BY) jacobi_step(const double *__r
 
 __global__ void jacobi_zero(unsigned long long *p) { *p = 0ull; }
 
+// ---------------------------------------------------------------- several iterations per launch
+// One launch per iteration is bound by the launch itself on small grids (7.7 us
+// per iteration at 1000x1500, whose 24 MB take 5 us from HBM and less from
+// cache) and by memory on large ones.  Here a workgroup loads a patch of 8*R x
+// 128 points once, runs t iterations on it in registers and writes back the
+// part whose values do not depend on anything outside the patch: all but a rim
+// of t points on the sides that have grid beyond them.  Neighbouring patches
+// overlap by that rim, so the extra work is the price of t - 1 passes over
+// memory and t - 1 launches.
+//   * A wave owns R rows of the patch, a lane two neighbouring columns:
+//     vertical neighbours are registers, horizontal ones the lane's other
+//     column or one whole-wave DPP shift, and only the first and last row of a
+//     wave go through LDS (two buffers by turns: one barrier per iteration).
+//   * Every value is formed by the same four operations in the same order as in
+//     jacobi_step, so the result has the same bits for any R, t and tiling.
+// Bound by instruction issue and the launches.  Measured, 64 iterations of
+// 1000x1500: 491 us one launch per iteration, 106 us as
+// four launches of 16 on 96-row patches.
+constexpr int JT_W = 8, JT_COLS = 128;
+
+template <int CTRL> __device__ __forceinline__ double wave_shift(double v)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// The wave's place in its patch and what stays fixed there.
+struct JacobiWave {
+    int wave, lane, i0, n;
+    bool fixed0, fixed1;  // the lane's columns lie on or outside the grid's boundary
+    bool out0, out1;      // the lane's columns are written by this workgroup
+    int ilo, ihi;         // and rows [ilo, ihi)
+};
+
+// One iteration on the wave's rows c[r][0..1].  EDGE: the patch touches the
+// grid's boundary (fixed values) or reaches past it.  WANT: returns the
+// largest change among the points this workgroup writes.
+template <int R, bool EDGE, bool WANT>
+__device__ __forceinline__ double jacobi_once(double (&c)[R][2], double (*b)[JT_W][JT_COLS], const JacobiWave &w)
+{
+    double ch = 0.0;
+    *reinterpret_cast<double2 *>(&b[0][w.wave][2 * w.lane]) = make_double2(c[0][0], c[0][1]);
+    *reinterpret_cast<double2 *>(&b[1][w.wave][2 * w.lane]) = make_double2(c[R - 1][0], c[R - 1][1]);
+    __syncthreads();
+    // past the patch's first and last wave: any value, it reaches only the rim
+    const double2 up = *reinterpret_cast<const double2 *>(&b[1][max(w.wave - 1, 0)][2 * w.lane]);
+    const double2 dn = *reinterpret_cast<const double2 *>(&b[0][min(w.wave + 1, JT_W - 1)][2 * w.lane]);
+    double u0 = up.x, u1 = up.y;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const double m0 = c[r][0], m1 = c[r][1];
+        const double d0 = r + 1 < R ? c[r + 1][0] : dn.x, d1 = r + 1 < R ? c[r + 1][1] : dn.y;
+        const double l0 = wave_shift<0x138>(m1);  // lane - 1's second column
+        const double r1 = wave_shift<0x130>(m0);  // lane + 1's first column
+        double s0 = u0 + d0, s1 = u1 + d1;
+        s0 = s0 + l0;
+        s1 = s1 + m0;
+        s0 = s0 + m1;
+        s1 = s1 + r1;
+        s0 = 0.25 * s0;
+        s1 = 0.25 * s1;
+        if (EDGE) {
+            const bool row = w.i0 + r <= 0 || w.i0 + r >= w.n - 1;
+            s0 = row || w.fixed0 ? m0 : s0;
+            s1 = row || w.fixed1 ? m1 : s1;
+        }
+        if (WANT && w.i0 + r >= w.ilo && w.i0 + r < w.ihi) {
+            if (w.out0) ch = fmax(ch, fabs(s0 - m0));
+            if (w.out1) ch = fmax(ch, fabs(s1 - m1));
+        }
+        c[r][0] = s0;
+        c[r][1] = s1;
+        u0 = m0;
+        u1 = m1;
+    }
+    return ch;
+}
+
+// hx, hy: rim of the patch on its vertical / horizontal sides (0: the grid
+// fits in that direction).  u == v only with a single workgroup.
+template <int R>
+__global__ void __launch_bounds__(64 * JT_W, 2) jacobi_tile(const double *u, double *v, int n, int m, int t, int hx, int hy,
+                                                            unsigned long long *max_change)
+{
+    constexpr int ROWS = R * JT_W;
+    __shared__ double rim[2][2][JT_W][JT_COLS];
+    JacobiWave w;
+    w.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    w.lane = threadIdx.x & 63;
+    w.n = n;
+    const int j0 = (int)blockIdx.x * (JT_COLS - 2 * hx) - hx, ib = (int)blockIdx.y * (ROWS - 2 * hy) - hy;
+    const int j = j0 + 2 * w.lane;
+    w.i0 = ib + w.wave * R;
+    // points outside the grid only ever meet fixed ones: load any point there
+    double c[R][2];
+    const int ja = min(max(j, 0), m - 1), jb = min(max(j + 1, 0), m - 1);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const double *p = u + (size_t)min(max(w.i0 + r, 0), n - 1) * m;
+        c[r][0] = p[ja];
+        c[r][1] = p[jb];
+    }
+    // what this workgroup writes: the patch without its rim
+    w.ilo = max(0, ib + hy);
+    w.ihi = min(n, ib + ROWS - hy);
+    const int jlo = max(0, j0 + hx), jhi = min(m, j0 + JT_COLS - hx);
+    w.out0 = j >= jlo && j < jhi;
+    w.out1 = j + 1 >= jlo && j + 1 < jhi;
+    w.fixed0 = j <= 0 || j >= m - 1;
+    w.fixed1 = j + 1 <= 0 || j + 1 >= m - 1;
+    const bool edge = ib <= 0 || ib + ROWS >= n || j0 <= 0 || j0 + JT_COLS >= m;
+    double ch = 0.0;
+    const int plain = max_change ? t - 1 : t;
+    if (edge) {
+        for (int it = 0; it < plain; ++it) jacobi_once<R, true, false>(c, rim[it & 1], w);
+    } else {
+        for (int it = 0; it < plain; ++it) jacobi_once<R, false, false>(c, rim[it & 1], w);
+    }
+    if (max_change) ch = jacobi_once<R, true, true>(c, rim[plain & 1], w);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (w.i0 + r < w.ilo || w.i0 + r >= w.ihi) continue;
+        double *q = v + (size_t)(w.i0 + r) * m + j;
+        if (w.out0) q[0] = c[r][0];
+        if (w.out1) q[1] = c[r][1];
+    }
+    if (max_change) {
+        for (int off = 32; off > 0; off >>= 1) ch = fmax(ch, __shfl_xor(ch, off));
+        if (w.lane == 0) atomicMax(max_change, (unsigned long long)__double_as_longlong(ch));
+    }
+}
+
 hipError_t launch_jacobi_step(const double *u, double *v, int n, int m, unsigned long long *max_change, hipStream_t s)
 {
     if (max_change) hipLaunchKernelGGL(jacobi_zero, dim3(1), dim3(1), 0, s, max_change);
     dim3 grid((m + JAC_BX - 1) / JAC_BX, (n + JAC_BY * JAC_STRIP - 1) / (JAC_BY * JAC_STRIP));
     hipLaunchKernelGGL(jacobi_step, grid, dim3(JAC_BX * JAC_BY), 0, s, u, v, n, m, max_change);
     return hipGetLastError();
+}
+
+// Workgroups of a patch height and iterations per launch; 0 if the rim leaves
+// nothing to write.
+static long jacobi_groups(int n, int m, int rows, int t)
+{
+    const int wx = m <= JT_COLS ? JT_COLS : JT_COLS - 2 * t, wy = n <= rows ? rows : rows - 2 * t;
+    if (wx <= 0 || wy <= 0) return 0;
+    return ((long)(m + wx - 1) / wx) * ((n + wy - 1) / wy);
+}
+
+// Rows per wave and launches for `iters` iterations: the least launches x
+// (launch + t x iteration) over patch heights and iterations per launch t.  A
+// launch costs about 6.5 us with its loads and stores; an iteration 0.15 us of
+// barrier and LDS latency and, per workgroup a CU runs at once, 96 clocks of
+// issue a row (two waves on each SIMD, 12 instructions for two columns).  At
+// 1000x1500 the rule takes 96-row patches and 16 iterations: 256 workgroups.
+// A grid that fits in one patch needs no rim and no partner buffer: one launch,
+// in place (at most 4096 iterations each, so that a launch stays short).
+JacobiPlan jacobi_plan(int n, int m, int iters)
+{
+    JacobiPlan best{0, 0, false};
+    double cost = 1e300;
+    for (int r = 4; r <= 16; r += 4) {
+        const int rows = r * JT_W;
+        if (n <= rows && m <= JT_COLS) return JacobiPlan{r, (iters + 4095) / 4096, true};
+        for (int t = 1; t <= 24 && t <= iters; ++t) {
+            const long g = jacobi_groups(n, m, rows, t);
+            if (g == 0) break;
+            if (n > rows && (n - 1) / (rows - 2 * t) >= 65535) break;  // the launch's grid limit
+            // an even number of launches ends in the buffer it began in; a single
+            // one is followed by a copy
+            long launches = ((long)iters + t - 1) / t;
+            if (launches > 1) launches += launches & 1;
+            const double per_cu = (double)((g + 255) / 256);
+            const double us = launches * (6.5 + (double)iters / launches * (0.15 + 0.0457 * r * per_cu)) + (launches == 1 ? 6.5 : 0.0);
+            if (us < cost) {
+                cost = us;
+                best = JacobiPlan{r, (int)launches, false};
+            }
+        }
+    }
+    return best;
+}
+
+template <int R>
+static hipError_t go_jacobi(const double *u, double *v, int n, int m, int t, unsigned long long *max_change, hipStream_t s)
+{
+    constexpr int ROWS = R * JT_W;
+    const int hx = m <= JT_COLS ? 0 : t, hy = n <= ROWS ? 0 : t;
+    if (t < 1 || 2 * hx >= JT_COLS || 2 * hy >= ROWS) return hipErrorInvalidValue;
+    const long gx = hx ? ((long)m + JT_COLS - 2 * hx - 1) / (JT_COLS - 2 * hx) : 1;
+    const long gy = hy ? ((long)n + ROWS - 2 * hy - 1) / (ROWS - 2 * hy) : 1;
+    if (gy > 65535 || (u == v && gx * gy > 1)) return hipErrorInvalidValue;
+    if (max_change) hipLaunchKernelGGL(jacobi_zero, dim3(1), dim3(1), 0, s, max_change);
+    hipLaunchKernelGGL(jacobi_tile<R>, dim3((unsigned)gx, (unsigned)gy), dim3(64 * JT_W), 0, s, u, v, n, m, t, hx, hy, max_change);
+    return hipGetLastError();
+}
+
+hipError_t launch_jacobi_tile(int rows, const double *u, double *v, int n, int m, int t, unsigned long long *max_change, hipStream_t s)
+{
+    switch (rows) {
+    case 4: return go_jacobi<4>(u, v, n, m, t, max_change, s);
+    case 8: return go_jacobi<8>(u, v, n, m, t, max_change, s);
+    case 12: return go_jacobi<12>(u, v, n, m, t, max_change, s);
+    case 16: return go_jacobi<16>(u, v, n, m, t, max_change, s);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace dnk

@@ -1826,12 +1826,21 @@ extern "C" dn_status dn_jacobi(double *u, double *work, int n, int m, int iters,
         if (max_change) HIPCHK(launch_zero_f32((float *)max_change, 2, s));  // a fill kernel, not a memset node
         return DN_OK;
     }
-    HIPCHK(hipMemcpyAsync(work, u, bytes, hipMemcpyDeviceToDevice, s));  // boundary values in both buffers
+    unsigned long long *mc = (unsigned long long *)max_change;
     double *a = u, *b = work;
-    for (int it = 0; it < iters; ++it) {
-        const bool last = it + 1 == iters;
-        HIPCHK(launch_jacobi_step(a, b, n, m, last ? (unsigned long long *)max_change : nullptr, s));
-        std::swap(a, b);
+    if (n < (1 << 19)) {
+        const JacobiPlan p = jacobi_plan(n, m, iters);
+        for (int k = 0, it = 0; k < p.launches; ++k) {
+            const int t = (iters - it + (p.launches - k) - 1) / (p.launches - k);
+            it += t;
+            HIPCHK(launch_jacobi_tile(p.rows, a, p.in_place ? a : b, n, m, t, it == iters ? mc : nullptr, s));
+            if (!p.in_place) std::swap(a, b);
+        }
+    } else {  // taller than the tiled launch's grid
+        for (int it = 0; it < iters; ++it) {
+            HIPCHK(launch_jacobi_step(a, b, n, m, it + 1 == iters ? mc : nullptr, s));
+            std::swap(a, b);
+        }
     }
     if (a != u) HIPCHK(hipMemcpyAsync(u, a, bytes, hipMemcpyDeviceToDevice, s));
     return DN_OK;
