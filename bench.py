@@ -44,7 +44,7 @@ def _tile_desc(dn, t: int) -> str:
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("conv.hip", "conv_pipe.hip", "conv_dev.h", "dn_kernels.h"):
+    for f in ("conv.hip", "conv_pipe.hip", "conv_direct.hip", "conv_dev.h", "dn_kernels.h"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
