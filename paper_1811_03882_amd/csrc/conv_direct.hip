@@ -672,7 +672,14 @@ hipError_t launch_conv_halo(int dt, const ConvArgs &a, hipStream_t s)
 //     while one is multiplied (one barrier per tile);
 //   * tiles are dealt out in runs of consecutive tiles per XCD, so the halo
 //     rows and columns that neighbouring tiles share are read through the
-//     same L2.
+//     same L2;
+//   * stores are counted, and the wait for a window leaves them in flight; an
+//     unpooled tile stores four channels of a pixel per lane and instruction
+//     (two bytes per lane before).  Input gradient of the nine-layer net, batch
+//     16, BF16, whose convs with argmax codes and to the image run here: 763 ->
+//     729 us.
+// Bound by issue and latency with two waves per SIMD (counters at 104x104x32 ->
+// 64 + pool, batch 64: matrix cores busy 33 %, VALU 39 %, waves waiting 44 %).
 
 // Output rows per tile: 16, or 8 for four 16-channel blocks (whose
 // accumulators and weights would not leave room for 16 rows).
@@ -693,14 +700,23 @@ __host__ __device__ constexpr int h2_nbp(int nb) { return nb == 4 ? 2 : nb; }
 // parts in turn.
 __device__ __forceinline__ int h2_row(int q, int nq, int i) { return 2 * (q + nq * (i >> 2)) + ((i >> 1) & 1); }
 
-// s_waitcnt vmcnt(n) for a run-time n in [0, 40] (larger n waits for 0).
-template <int N> __device__ __forceinline__ void wait_vm_upto(int n)
+// s_waitcnt vmcnt(at most n) for a wave-uniform run-time n: the largest of a few
+// constants not above it.
+__device__ __forceinline__ void wait_vm_upto(int n)
 {
-    if constexpr (N > 0) {
-        if (n == N) { wait_vm<N>(); return; }
-        wait_vm_upto<N - 1>(n);
+    if (n >= 32) {
+        if (n >= 48) { if (n >= 60) wait_vm<60>(); else wait_vm<48>(); }
+        else { if (n >= 40) wait_vm<40>(); else wait_vm<32>(); }
+    } else if (n >= 16) {
+        if (n >= 24) { if (n >= 28) wait_vm<28>(); else wait_vm<24>(); }
+        else { if (n >= 20) wait_vm<20>(); else wait_vm<16>(); }
+    } else if (n >= 8) {
+        if (n >= 12) { if (n >= 14) wait_vm<14>(); else wait_vm<12>(); }
+        else { if (n >= 10) wait_vm<10>(); else wait_vm<8>(); }
     } else {
-        wait_vm<0>();
+        if (n >= 4) { if (n >= 6) wait_vm<6>(); else wait_vm<4>(); }
+        else if (n >= 2) wait_vm<2>();
+        else wait_vm<0>();
     }
 }
 
@@ -814,21 +830,30 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
 #pragma unroll
     for (int i = 0; i < BPW; ++i)
         pbb[i] = (h2_row(wq, NQ, i) * a.stride * LW + (16 * (i & 1) + lrow) * a.stride) * pst * 16;
-    float bias[NBP], scl[NBP];
+    // pooled: a lane's accumulators are one channel of four pixels (pixels are
+    // MFMA operand A); else four channels of one pixel (weights are operand A)
+    constexpr int CH = POOL ? 1 : 4;
+    float bias[NBP][CH], scl[NBP][CH];
 #pragma unroll
-    for (int nb = 0; nb < NBP; ++nb) {
-        const int col = (wg * NBP + nb) * 16 + lrow;
-        bias[nb] = col < a.cout_p ? a.bias[col] : 0.0f;
-        scl[nb] = (DT == FP8 && col < a.cout_p) ? a.wscale[col] * a.in_scale : 1.0f;
-    }
+    for (int nb = 0; nb < NBP; ++nb)
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int col = (wg * NBP + nb) * 16 + (POOL ? lrow : 4 * lgrp + i);
+            bias[nb][i] = col < a.cout_p ? a.bias[col] : 0.0f;
+            scl[nb][i] = (DT == FP8 && col < a.cout_p) ? a.wscale[col] * a.in_scale : 1.0f;
+        }
     const int Hp = a.Ho >> 1, Wp = a.Wo >> 1;
     const size_t img = POOL ? (size_t)Hp * Wp * a.cout_p : (size_t)a.Ho * a.Wo * a.cout_p;
     const float lsl = act_slope(a.act, a.slope);
 
+    int st1 = 0, st2 = 0, st3 = 0;  // vector stores this wave issued for tiles k - 1, k - 2, k - 3
     for (int k = 0; k < my_tiles; ++k) {
-        // this wave's transfers of tile k landed (loads complete in order; the
-        // ones still allowed in flight are those of the tiles issued after it)
-        wait_vm_upto<40>(min(nbuf - 2, my_tiles - 1 - k) * dw);
+        // this wave's transfers of tile k landed.  Vector memory operations
+        // complete in order, so whatever was issued after them may stay in
+        // flight: the transfers of the next tiles and the stores of the last
+        // nbuf - 1 (waiting for those too exposed their way to memory in every
+        // tile).  The count never exceeds what was issued.
+        wait_vm_upto(min(nbuf - 2, my_tiles - 1 - k) * dw + st1 + (nbuf > 2 ? st2 : 0) + (nbuf > 3 ? st3 : 0));
         // the barrier: every wave's transfers landed and every wave is done
         // with tile k - 1's buffer
         lds_barrier();
@@ -857,67 +882,96 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
 #pragma unroll
                 for (int i = 0; i < BPW; ++i)
 #pragma unroll
-                    for (int nb = 0; nb < NBP; ++nb) mma<DT>(acc[i][nb], af[i], wr[nb][ks]);
+                    for (int nb = 0; nb < NBP; ++nb) {
+                        if constexpr (POOL) mma<DT>(acc[i][nb], af[i], wr[nb][ks]);
+                        else mma<DT>(acc[i][nb], wr[nb][ks], af[i]);
+                    }
             }
         }
 
-        // epilogue: bias, activation, [residual], [2x2 max], round, NHWC store
+        // epilogue: bias, activation, [residual], [2x2 max], round, NHWC store.
+        // Stores go through a buffer resource the size of the image's output: an
+        // element past the right edge or the channels gets an offset past it,
+        // which the store drops, so every wave issues a number it can count.
         unsigned char *yimg = reinterpret_cast<unsigned char *>(a.y) + (size_t)n * img * ES;
         const unsigned char *rimg = a.res ? reinterpret_cast<const unsigned char *>(a.res) + (size_t)n * img * ES : nullptr;
         const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void *)yimg, (short)0, (int)(img * ES), 0x00020000);
+        int stores = 0;
+        if constexpr (POOL) {
+            const __amdgpu_buffer_rsrc_t ram = __builtin_amdgcn_make_buffer_rsrc(
+                AM ? (void *)(a.argmax + (size_t)n * img) : nullptr, (short)0, AM ? (int)img : 0, 0x00020000);
 #pragma unroll
-        for (int nb = 0; nb < NBP; ++nb) {
-            const int col = (wg * NBP + nb) * 16 + lrow;
-            if (col >= a.cout_p) continue;
-            if constexpr (POOL) {
+            for (int nb = 0; nb < NBP; ++nb) {
+                const int col = (wg * NBP + nb) * 16 + lrow;
                 // blocks i (row 2k) and i + 2 (row 2k + 1) of the same column
-                // half: lane column pairs (4*lgrp + 2j, + 1) are the windows
+                // half: lane column pairs (4*lgrp + 2j, + 1) are the windows.
                 // The store offset is a wave-uniform part (window row, the
-                // block's first window) plus a lane part; a window past the
-                // right edge gets an offset past the image's output, which
-                // the buffer store drops.
+                // block's first window) plus a lane part.
 #pragma unroll
                 for (int i = 0; i < BPW; ++i) {
                     if (i & 2) continue;
                     const int hp = (th0 + h2_row(wq, NQ, i)) >> 1;
-                    if (hp >= Hp) continue;
+                    if (hp >= Hp) continue;  // wave-uniform
                     const int wpb = (tw0 + 16 * (i & 1)) >> 1;
-                    const int soff = (hp * Wp + wpb) * a.cout_p * ES;
+                    const int soff = (hp * Wp + wpb) * a.cout_p;
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         const float w4[4] = {acc[i][nb][2 * j], acc[i][nb][2 * j + 1], acc[i + 2][nb][2 * j],
                                              acc[i + 2][nb][2 * j + 1]};
                         const float mx = fmaxf(fmaxf(w4[0], w4[1]), fmaxf(w4[2], w4[3]));
-                        const float o = activate_sel(mx * scl[nb] + bias[nb], lsl) * a.out_inv_scale;
-                        const int wp = wpb + 2 * lgrp + j;
-                        const int voff = wp < Wp ? ((2 * lgrp + j) * a.cout_p + col) * ES : (int)DN_OOB;
-                        if constexpr (DT == F32) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), ry, voff, soff, 0);
-                        else if constexpr (DT == BF16) __builtin_amdgcn_raw_buffer_store_b16(f2bf(o), ry, voff, soff, 0);
-                        else __builtin_amdgcn_raw_buffer_store_b8(f2e4m3(o), ry, voff, soff, 0);
-                        if constexpr (AM) {
-                            if (wp < Wp)
-                                a.argmax[(size_t)n * img + (hp * Wp + wp) * a.cout_p + col] =
-                                    window_argmax<DT>(w4, scl[nb], bias[nb], a.act, a.slope, a.out_inv_scale);
-                        }
+                        const float o = activate_sel(mx * scl[nb][0] + bias[nb][0], lsl) * a.out_inv_scale;
+                        const bool ok = wpb + 2 * lgrp + j < Wp && col < a.cout_p;
+                        const int loff = (2 * lgrp + j) * a.cout_p + col;
+                        const int voff = ok ? loff * ES : (int)DN_OOB;
+                        if constexpr (DT == F32) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), ry, voff, soff * ES, 0);
+                        else if constexpr (DT == BF16) __builtin_amdgcn_raw_buffer_store_b16(f2bf(o), ry, voff, soff * ES, 0);
+                        else __builtin_amdgcn_raw_buffer_store_b8(f2e4m3(o), ry, voff, soff * ES, 0);
+                        if constexpr (AM)
+                            __builtin_amdgcn_raw_buffer_store_b8(
+                                window_argmax<DT>(w4, scl[nb][0], bias[nb][0], a.act, a.slope, a.out_inv_scale), ram,
+                                ok ? loff : (int)DN_OOB, soff, 0);
                     }
+                    stores += AM ? 4 : 2;
                 }
-            } else {
+            }
+        } else {
+#pragma unroll
+            for (int nb = 0; nb < NBP; ++nb) {
+                const int ch = (wg * NBP + nb) * 16 + 4 * lgrp;  // cout_p is a multiple of 4
 #pragma unroll
                 for (int i = 0; i < BPW; ++i) {
                     const int ho = th0 + h2_row(wq, NQ, i);
-                    if (ho >= a.Ho) continue;
+                    if (ho >= a.Ho) continue;  // wave-uniform
+                    const int wob = tw0 + 16 * (i & 1);
+                    const int soff = (ho * a.Wo + wob) * a.cout_p;
+                    const bool ok = wob + lrow < a.Wo && ch < a.cout_p;
+                    const int loff = lrow * a.cout_p + ch;
+                    float v[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int wo = tw0 + 16 * (i & 1) + 4 * lgrp + q;
-                        if (wo >= a.Wo) continue;
-                        const int o = (ho * a.Wo + wo) * a.cout_p + col;
-                        float r = activate_sel(acc[i][nb][q] * scl[nb] + bias[nb], lsl);
-                        if (rimg) r += load_el<DT>(rimg, o) * a.res_scale;
-                        store_el<DT>(yimg, o, r * a.out_inv_scale);
+                    for (int q = 0; q < 4; ++q) v[q] = activate_sel(acc[i][nb][q] * scl[nb][q] + bias[nb][q], lsl);
+                    if (rimg) {
+                        float r[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                        if (ok) load4<DT>(rimg, (size_t)soff + loff, r);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[q] += r[q] * a.res_scale;
                     }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] *= a.out_inv_scale;
+                    const int voff = ok ? loff * ES : (int)DN_OOB;
+                    if constexpr (DT == F32) {
+                        __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])}, ry, voff, soff * ES, 0);
+                    } else if constexpr (DT == BF16) {
+                        __builtin_amdgcn_raw_buffer_store_b64(u32x2{(unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16), (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16)}, ry, voff, soff * ES, 0);
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b32((unsigned)f2e4m3(v[0]) | ((unsigned)f2e4m3(v[1]) << 8) | ((unsigned)f2e4m3(v[2]) << 16) | ((unsigned)f2e4m3(v[3]) << 24), ry, voff, soff * ES, 0);
+                    }
+                    ++stores;
                 }
             }
         }
+        st3 = st2;
+        st2 = st1;
+        st1 = stores;
     }
 }
 
