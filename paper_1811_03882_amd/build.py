@@ -21,7 +21,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libdn.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["conv.hip", "conv_pipe.hip", "conv_direct.hip", "aux.hip", "backward.hip", "detect.hip", "jacobi.hip", "runtime.cpp"]
+SOURCES = ["conv.hip", "conv_pipe.hip", "conv_direct.hip", "conv_unpool.hip", "aux.hip", "backward.hip", "detect.hip", "jacobi.hip", "runtime.cpp"]
 HOST_SOURCES = ["cpu_layers.cpp", "ga.cpp"]
 ARCH = "gfx950"
 

@@ -153,18 +153,18 @@ template <int DT> __device__ __forceinline__ float stored_value(float v)
 // Index (2*dy + dx) of the first maximal stored output of a 2x2 window whose
 // accumulators are acc[0..3] in row-major window order: the branch the
 // max-pool gradient follows.
-// The output is activate(acc * scl + bias) * post, as in the caller's epilogue.
+// The output is activate(acc * scl + bias) * post, as in the caller's epilogue:
+// monotone in acc, so the largest stored value is the stored value of the
+// largest accumulator, and the first element that reaches it is looked for
+// among three.  A NaN is never larger than anything, and stays the choice where
+// it comes first.
 template <int DT> __device__ __forceinline__ unsigned char window_argmax(const float *acc, float scl, float bias,
                                                                         int act, float slope, float post)
 {
-    int k = 0;
-    float m = stored_value<DT>(activate(acc[0] * scl + bias, act, slope) * post);
-#pragma unroll
-    for (int q = 1; q < 4; ++q) {
-        const float o = stored_value<DT>(activate(acc[q] * scl + bias, act, slope) * post);
-        if (o > m) { m = o; k = q; }
-    }
-    return (unsigned char)k;
+    const auto stored = [&](float v) { return stored_value<DT>(activate(v * scl + bias, act, slope) * post); };
+    const float m = stored(fmaxf(fmaxf(acc[0], acc[1]), fmaxf(acc[2], acc[3])));
+    const unsigned char tail = stored(acc[1]) == m ? 1 : stored(acc[2]) == m ? 2 : 3;
+    return stored(acc[0]) < m ? tail : 0;
 }
 
 // ---------------------------------------------------------------- the kernel
@@ -401,5 +401,14 @@ __device__ __forceinline__ void dma16(const i32x4 &rsrc, unsigned voff, const vo
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
+
+// Division by a runtime divisor d >= 1 without the integer-divide sequence:
+// q = umulhi(n, ceil(2^32 / d)) is exact whenever n * d < 2^32 (true for
+// every LDS index here).
+struct FastDiv {
+    unsigned m, d;
+    __device__ explicit FastDiv(unsigned d_) : m(d_ > 1 ? 0xFFFFFFFFu / d_ + 1u : 0u), d(d_) {}
+    __device__ __forceinline__ unsigned div(unsigned n) const { return d > 1 ? __umulhi(n, m) : n; }
+};
 
 }  // namespace dnk

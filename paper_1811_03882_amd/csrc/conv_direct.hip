@@ -252,6 +252,8 @@ __global__ void __launch_bounds__(256) conv_first(FirstArgs a)
         // moved past the size) is dropped without a branch.
         const __amdgpu_buffer_rsrc_t ry =
             __builtin_amdgcn_make_buffer_rsrc((void *)yimg, (short)0, (int)((size_t)Hy * Wy * a.cout_p * ES), 0x00020000);
+        const __amdgpu_buffer_rsrc_t ram = __builtin_amdgcn_make_buffer_rsrc(
+            AM ? (void *)(a.argmax + (size_t)n * Hy * Wy * a.cout_p) : nullptr, (short)0, AM ? Hy * Wy * a.cout_p : 0, 0x00020000);
         const unsigned lane_off = (unsigned)((lgrp * a.cout_p + lrow) * ES);
         const int bands = min(a.th >> 1, Hy - (th0 >> 1));
         for (int band = 0; band < bands; ++band) {
@@ -283,11 +285,10 @@ __global__ void __launch_bounds__(256) conv_first(FirstArgs a)
                     else if constexpr (DT == BF16) __builtin_amdgcn_raw_buffer_store_b16(f2bf(o), ry, voff, soff, 0);
                     else __builtin_amdgcn_raw_buffer_store_b8(f2e4m3(o), ry, voff, soff, 0);
                     if constexpr (AM) {
-                        if (ok) {
-                            const float w4[4] = {acc[0], acc[1], acc[2], acc[3]};
-                            a.argmax[(size_t)n * Hy * Wy * a.cout_p + (hp * Wy + wpb + lgrp) * a.cout_p + col] =
-                                window_argmax<DT>(w4, scl4[nb][0], bias4[nb][0], a.act, a.slope, opost);
-                        }
+                        const float w4[4] = {acc[0], acc[1], acc[2], acc[3]};
+                        __builtin_amdgcn_raw_buffer_store_b8(window_argmax<DT>(w4, scl4[nb][0], bias4[nb][0], a.act, a.slope, opost), ram,
+                                                             ok ? lgrp * a.cout_p + lrow : (int)0x80000000u,
+                                                             (hp * Wy + wpb) * a.cout_p + nb * 16, 0);
                     }
                 }
             }
@@ -389,15 +390,6 @@ hipError_t launch_conv_first(int dt, const FirstArgs &a, hipStream_t s)
 #undef DN_FIRST_CP
     return hipGetLastError();
 }
-
-// Division by a runtime divisor d >= 1 without the integer-divide sequence:
-// q = umulhi(n, ceil(2^32 / d)) is exact whenever n * d < 2^32 (true for
-// every LDS index here).
-struct FastDiv {
-    unsigned m, d;
-    __device__ explicit FastDiv(unsigned d_) : m(d_ > 1 ? 0xFFFFFFFFu / d_ + 1u : 0u), d(d_) {}
-    __device__ __forceinline__ unsigned div(unsigned n) const { return d > 1 ? __umulhi(n, m) : n; }
-};
 
 // ---------------------------------------------------------------- halo kernel
 // Small convolutions (K = R*S*Cin_p up to HALO_KMAX elements, Cout <= 64):

@@ -155,6 +155,22 @@ hipError_t launch_maxpool_bwd(int dt, const void *x, const void *dy, void *dx, i
 // argmax[n][i][j][c] == 2*dy + dx, else 0; every element of dz is written.
 hipError_t launch_unpool_bwd(int dt, const unsigned char *argmax, const void *pooled, const void *dy, void *dz, int n,
                              int hp, int wp, int cp, float mask, hipStream_t s);
+// Backward-data conv (stride 1, linear, no accumulation) of a forward conv whose
+// 2x2/2 pool ran fused, reading the pooled gradient: launch_unpool_bwd and the
+// conv over its result in one kernel, the same bits (conv_unpool.hip).
+struct UnpoolConvArgs {
+    const unsigned char *argmax;   // [batch][Hp][Wp][cp]
+    const void *pooled, *dy;       // [batch][Hp][Wp][cp]: pooled outputs, gradient of them
+    const void *w;                 // packed backward weights [cout_p][k_pad]
+    void *y;                       // dx [batch][Ho][Wo][cout_p], or (image) [batch][C][Ho][Wo] FP32
+    int batch, Hp, Wp, cp;
+    int Ho, Wo, cout_p, C;
+    int R, S, pad, k_pad;          // pad of the backward conv: k - 1 - the forward's
+    float mask;                    // leaky slope, < 0: linear
+    int image;
+};
+bool unpool_conv_ok(int dt, const UnpoolConvArgs &a);
+hipError_t launch_conv_unpool(int dt, const UnpoolConvArgs &a, hipStream_t s);
 // z[n][hz][wz][cp] = dy[n][i/stride][j/stride] where stride divides i and j, else 0.
 hipError_t launch_dilate(int dt, const void *dy, void *z, int n, int ho, int wo, int cp, int hz, int wz, int stride,
                          hipStream_t s);

@@ -2541,6 +2541,34 @@ static dn_status make_bwd_plan(const dn_net *net, int target, int batch, int h, 
     return DN_OK;
 }
 
+// The backward of op k of the pass (a conv with a fused pool) as one kernel,
+// where its shape allows: a stride-1 conv of few channels whose input's gradient
+// has no earlier contribution.  image: it is the network's first layer.
+static bool bwd_unpool_args(const dn_net *net, const BwdPlan &b, int k, char *base, UnpoolConvArgs *out)
+{
+    const Plan &p = b.p;
+    const Op &op = p.ops[k];
+    if (op.kind != OP_CONV || !op.pool || b.acc[k]) return false;
+    const dn_conv_desc &f = b.fwd[k];
+    if (f.stride != 1 || f.pad > f.ksize - 1) return false;
+    const ConvWeights &cw = net->cw[op.conv];
+    const Value &vi = p.vals[op.in];
+    UnpoolConvArgs a{};
+    a.argmax = (const unsigned char *)(base + op.argmax_off);
+    a.pooled = base + p.vals[op.out].off;
+    a.dy = base + b.goff[op.out];
+    a.w = cw.wb;
+    a.image = op.in == 0;
+    a.y = base + (a.image ? b.gin_off : b.goff[op.in]);
+    a.batch = p.batch; a.Hp = op.Ho; a.Wp = op.Wo; a.cp = op.cout_p;
+    a.Ho = vi.h; a.Wo = vi.w; a.cout_p = vi.cp; a.C = vi.c;
+    a.R = a.S = f.ksize; a.pad = f.ksize - 1 - f.pad; a.k_pad = cw.kb_pad;
+    a.mask = f.activation == DN_ACT_LEAKY ? net->o.leaky_slope : -1.0f;
+    if (!unpool_conv_ok(p.dtype, a)) return false;
+    *out = a;
+    return true;
+}
+
 static dn_status enqueue_input_gradient(const dn_net *net, const BwdPlan &b, char *base, const float *x, hipStream_t s)
 {
     const Plan &p = b.p;
@@ -2557,7 +2585,12 @@ static dn_status enqueue_input_gradient(const dn_net *net, const BwdPlan &b, cha
         char *gout = base + b.goff[op.out];
         const Value &vo = p.vals[op.out];
         const size_t count = (size_t)p.batch * vo.h * vo.w * vo.cp;
-        if (op.kind == OP_CONV && op.pool) {
+        UnpoolConvArgs ua;
+        if (bwd_unpool_args(net, b, k, base, &ua)) {
+            HIPCHK(launch_conv_unpool(dt, ua, s));
+            if (ua.image) return DN_OK;  // the image's gradient left as NCHW FP32
+            have[op.in] = 1;
+        } else if (op.kind == OP_CONV && op.pool) {
             // fused 2x2/2 pool: each window's gradient goes to its argmax element,
             // times the leaky gradient there (the pooled output has its sign)
             const dn_layer_desc &d = net->L[op.conv];
@@ -2694,6 +2727,15 @@ extern "C" dn_status dn_input_gradient_readback(const dn_net *net, void *arena, 
     if (out_bytes < need) return fail(DN_EINVAL, "readback: output buffer has %zu bytes, needs %zu", out_bytes, need);
     hipStream_t s = (hipStream_t)stream;
     char *base = (char *)arena;
+    if (what == 2) {  // a full-size gradient that the pass only formed tile by tile
+        for (int k = 0; k < b.nops; ++k) {
+            const Op &op = p.ops[k];
+            UnpoolConvArgs ua;
+            if (op.kind != OP_CONV || !op.pool || op.conv != of_layer || !bwd_unpool_args(net, b, k, base, &ua)) continue;
+            HIPCHK(launch_unpool_bwd(p.dtype, ua.argmax, ua.pooled, ua.dy, base + b.goff[v], p.batch, op.Ho, op.Wo, op.cout_p,
+                                     ua.mask, s));
+        }
+    }
     if (what == 1)
         HIPCHK(hipMemcpyAsync(out, base + fused->argmax_off, need, hipMemcpyDeviceToDevice, s));
     else
@@ -2802,7 +2844,8 @@ static dn_status autotune_backward(dn_net *net, int layer, int batch, int h, int
     // the backward-data convs
     for (int k = 0; k < b.nops; ++k) {
         const Op &op = p.ops[k];
-        if (op.kind != OP_CONV) continue;
+        UnpoolConvArgs ua;
+        if (op.kind != OP_CONV || bwd_unpool_args(net, b, k, base, &ua)) continue;
         const dn_conv_desc &f = b.fwd[k];
         const std::string sig = bwd_sig(&f, b.acc[k]);
         if (net->tuned.count(sig)) continue;
