@@ -258,6 +258,19 @@ __device__ __forceinline__ f4 load16_dev(const float *base, unsigned off)
     return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 16));
 }
 
+// Four channels col..col+3 of output pixel m as NCHW FP32: the value a consumer
+// of the stored tensor would read, in the caller's layout.
+template <int DT> __device__ __forceinline__ void store4_nchw(float *y, int C, int HW, float scale, unsigned m, int col, const float *v)
+{
+    const unsigned n = m / (unsigned)HW, p = m - n * (unsigned)HW;
+    float *q = y + ((size_t)n * C + col) * HW + p;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float s = stored_value<DT>(v[i]);
+        if (col + i < C) q[(size_t)i * HW] = DT == FP8 ? s * scale : s;
+    }
+}
+
 // Split-K finish of one output group: rows (2x2 windows when pooled) `ro`,
 // channels col..col+3 (cout_p is a multiple of 4): the partial sums added in
 // split order, then the same epilogue as the unsplit path, one vector store.
@@ -323,7 +336,8 @@ template <int DT, bool DEV = false> __device__ __forceinline__ void splitk_finis
 #pragma unroll
         for (int j = 0; j < 4; ++j) o[j] *= a.out_inv_scale;
     }
-    store4<DT>(a.y, ro * a.cout_p + col, o);
+    if (a.nchw) store4_nchw<DT>(a.nchw, a.nchw_c, a.Ho * a.Wo, a.nchw_scale, (unsigned)ro, col, o);
+    else store4<DT>(a.y, ro * a.cout_p + col, o);
 }
 
 // In-kernel split-K finish (a.tile_count set).  Each split's workgroup of an

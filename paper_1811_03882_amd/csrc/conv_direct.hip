@@ -75,11 +75,14 @@ __device__ __forceinline__ unsigned mad_u24(int s, int v, int c)
 }
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
-// AM (with POOL): also store each window's argmax code (a.argmax); a template
-// flag so that the forward's own instantiations carry none of that code.
-template <int DT, bool POOL, int CP, bool AM = false, int NBM = FIRST_MAX_COUT / 16>
+// MODE FIRST_ARGMAX (with POOL): also store each window's argmax code
+// (a.argmax); FIRST_NCHW: the result leaves as a.nchw.  A template flag so that
+// the plain instantiations, bound by instruction issue, carry none of that code.
+enum { FIRST_PLAIN = 0, FIRST_ARGMAX = 1, FIRST_NCHW = 2 };
+template <int DT, bool POOL, int CP, int MODE = FIRST_PLAIN, int NBM = FIRST_MAX_COUT / 16>
 __global__ void __launch_bounds__(256) conv_first(FirstArgs a)
 {
+    constexpr bool AM = MODE == FIRST_ARGMAX;
     constexpr int ES = esize(DT), SEG = seg_el(DT);
     constexpr int SPL = Tr<DT>::SPL, KSTEP = first_kstep(DT);
     constexpr int KPL = KSTEP / 4;                               // K elements per lane per step
@@ -146,6 +149,8 @@ __global__ void __launch_bounds__(256) conv_first(FirstArgs a)
         if (a.x8) stage(std::true_type{});
         else stage(std::false_type{});
     }
+
+    for (int i = blockIdx.x * 256 + tid; i < a.nzero; i += gridDim.x * 256) a.zero[i] = 0u;
 
     // 16 zero bytes after the window: read units past row R or tap S read here
     const int zaddr = (LH * LW * PIXB + 15) & ~15;
@@ -281,6 +286,12 @@ __global__ void __launch_bounds__(256) conv_first(FirstArgs a)
                     const bool ok = wok && col < a.cout_p;
                     const int soff = ((hp * Wy + wpb) * a.cout_p + nb * 16) * ES;
                     const int voff = ok ? (int)lane_off : (int)0x80000000u;
+                    if constexpr (MODE == FIRST_NCHW) {
+                        const float s = stored_value<DT>(o);
+                        if (ok && col < a.nchw_c)
+                            a.nchw[(((size_t)n * a.nchw_c + col) * Hy + hp) * Wy + wpb + lgrp] = DT == FP8 ? s * a.nchw_scale : s;
+                        continue;
+                    }
                     if constexpr (DT == F32) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), ry, voff, soff, 0);
                     else if constexpr (DT == BF16) __builtin_amdgcn_raw_buffer_store_b16(f2bf(o), ry, voff, soff, 0);
                     else __builtin_amdgcn_raw_buffer_store_b8(f2e4m3(o), ry, voff, soff, 0);
@@ -313,7 +324,10 @@ __global__ void __launch_bounds__(256) conv_first(FirstArgs a)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = activate_sel(acc[i] * scl4[nb][i] + bias4[nb][i], lsl) * opost;
                 const int ho = th0 + bho, wo = tw0 + bwo + lrow;
-                if (ho < a.Ho && ch0 < a.cout_p && wo < a.Wo) store4<DT>(yimg, (ho * a.Wo + wo) * a.cout_p + ch0, v);
+                if (ho < a.Ho && ch0 < a.cout_p && wo < a.Wo) {
+                    if constexpr (MODE == FIRST_NCHW) store4_nchw<DT>(a.nchw + (size_t)n * a.nchw_c * a.Ho * a.Wo, a.nchw_c, a.Ho * a.Wo, a.nchw_scale, (unsigned)(ho * a.Wo + wo), ch0, v);
+                    else store4<DT>(yimg, (ho * a.Wo + wo) * a.cout_p + ch0, v);
+                }
             }
         }
     }
@@ -332,6 +346,15 @@ static int first_tile_h(int dt, int C, int R, int S, int stride)
     if (first_lds_for(C, R, S, stride, 32, dt) <= 20 * 1024) return 32;
     return first_lds_for(C, R, S, stride, 16, dt) <= FIRST_LDS_MAX ? 16 : 8;
 }
+// Fewer rows, down to 4, while the tiles do not give every CU one: a small batch
+// is bound by the longest tile, not by the halo rows (32x32, batch 1, FP32: 8.6
+// us on two tiles of 16 rows, 5.4 us on eight of 4).
+static int first_tile_h(int dt, const FirstArgs &a)
+{
+    int th = first_tile_h(dt, a.C, a.R, a.S, a.stride);
+    while (th > 4 && (long)((a.Wo + FT_W - 1) / FT_W) * ((a.Ho + th - 1) / th) * a.batch < 256) th /= 2;
+    return th;
+}
 size_t first_lds_bytes(int dt, int C, int R, int S, int stride)
 {
     return first_lds_for(C, R, S, stride, first_tile_h(dt, C, R, S, stride), dt);
@@ -340,7 +363,7 @@ size_t first_lds_bytes(int dt, int C, int R, int S, int stride)
 hipError_t launch_conv_first(int dt, const FirstArgs &a, hipStream_t s)
 {
     FirstArgs b = a;
-    b.th = first_tile_h(dt, a.C, a.R, a.S, a.stride);
+    b.th = first_tile_h(dt, a);
     const size_t lds = first_lds_for(a.C, a.R, a.S, a.stride, b.th, dt);
     // one image's input planes (up to the padded channel count) and output
     // are addressed through buffer resources with 31-bit offsets
@@ -370,13 +393,19 @@ hipError_t launch_conv_first(int dt, const FirstArgs &a, hipStream_t s)
     } while (0)
 #define DN_FIRST(D)                                                                                  \
     do {                                                                                             \
-        if (b.pool) DN_FIRST_P(D, true, false);                                                      \
-        else DN_FIRST_P(D, false, false);                                                            \
+        if (b.nchw) {                                                                                \
+            if (b.pool) DN_FIRST_P(D, true, FIRST_NCHW);                                             \
+            else DN_FIRST_P(D, false, FIRST_NCHW);                                                   \
+        } else if (b.pool) {                                                                         \
+            DN_FIRST_P(D, true, FIRST_PLAIN);                                                        \
+        } else {                                                                                     \
+            DN_FIRST_P(D, false, FIRST_PLAIN);                                                       \
+        }                                                                                            \
     } while (0)
     if (b.argmax && (!b.pool || dt == FP8)) return hipErrorInvalidValue;
     if (b.argmax) {  // the input-gradient pass (F32 / BF16)
-        if (dt == F32) DN_FIRST_P(F32, true, true);
-        else DN_FIRST_P(BF16, true, true);
+        if (dt == F32) DN_FIRST_P(F32, true, FIRST_ARGMAX);
+        else DN_FIRST_P(BF16, true, FIRST_ARGMAX);
         return hipGetLastError();
     }
     switch (dt) {
@@ -631,8 +660,11 @@ static hipError_t go_halo_dt(const ConvArgs &a, int th, dim3 grid, size_t lds, h
 hipError_t launch_conv_halo(int dt, const ConvArgs &a, hipStream_t s)
 {
     if (!halo_ok(dt, a)) return hipErrorInvalidValue;
-    // 16-row tiles when two workgroups still fit in a CU's LDS, else 8 rows
-    const int th = halo_lds_bytes(dt, a, 16) <= 80 * 1024 ? 16 : 8;
+    // 16-row tiles when two workgroups still fit in a CU's LDS and there are
+    // enough of them for every CU, else 8 rows (208x208x16 -> 32, FP32, batch 1:
+    // 18.4 us on 91 tiles of 16 rows, 11.7 on 182 of 8)
+    const long tiles16 = (long)((a.Wo + HT_W - 1) / HT_W) * ((a.Ho + 15) / 16) * a.batch;
+    const int th = halo_lds_bytes(dt, a, 16) <= 80 * 1024 && tiles16 >= 256 ? 16 : 8;
     dim3 grid((a.Wo + HT_W - 1) / HT_W, (a.Ho + th - 1) / th, a.batch);
     const size_t lds = halo_lds_bytes(dt, a, th);
     switch (dt) {

@@ -106,7 +106,8 @@ __device__ __forceinline__ void pipe_epilogue(const ConvArgs &a, f4 (&acc)[FM][F
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] *= a.out_inv_scale;
-            store4<DT>(a.y, o, v);
+            if (a.nchw) store4_nchw<DT>(a.nchw, a.nchw_c, a.Ho * a.Wo, a.nchw_scale, (unsigned)m, col, v);
+            else store4<DT>(a.y, o, v);
         }
     }
 }

@@ -60,6 +60,12 @@ struct ConvArgs {
     // (splitk_counters()); set, the last split to finish a tile runs the
     // split-K finish itself, else launch_splitk_reduce must follow
     unsigned *tile_count;
+    // the network's last conv, may be nullptr: the output leaves as the caller's
+    // NCHW FP32 tensor of nchw_c channels instead of y (the stored value times
+    // nchw_scale, as the egress kernel makes it); pipelined tiles without a pool
+    float *nchw;
+    int nchw_c;
+    float nchw_scale;
 };
 
 // First convolution of a network, reading the NCHW FP32 input directly.
@@ -78,6 +84,11 @@ struct FirstArgs {
     float in_scale, out_inv_scale;
     int th;                // output rows per tile (set by launch_conv_first)
     unsigned char *argmax; // pool = 1 only, may be nullptr: as ConvArgs::argmax
+    float *nchw;           // may be nullptr: as ConvArgs::nchw
+    int nchw_c;
+    float nchw_scale;
+    unsigned *zero;        // may be nullptr: nzero words this launch also clears (the split-K
+    int nzero;             // tile counters of the convs behind it)
 };
 // Channels of one staged window pixel: C rounded up to 4, 8 or 16.
 __host__ __device__ constexpr int first_cp(int C) { return C <= 4 ? 4 : (C <= 8 ? 8 : 16); }
