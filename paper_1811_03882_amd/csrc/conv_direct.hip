@@ -719,10 +719,9 @@ constexpr int H2_MAXBLK = 16;  // 1 KB window blocks one wave transfers per tile
 __host__ __device__ constexpr int h2_pitch(int cps) { return (cps & 1) ? cps + 2 : cps + 1; }
 // 16-channel blocks per wave: every block up to 3, two of four.
 __host__ __device__ constexpr int h2_nbp(int nb) { return nb == 4 ? 2 : nb; }
-// Tile row of block i of pixel part q (of nq): blocks come as (row pair, row
-// in pair, column half), column half fastest; row pairs are dealt to the
-// parts in turn.
-__device__ __forceinline__ int h2_row(int q, int nq, int i) { return 2 * (q + nq * (i >> 2)) + ((i >> 1) & 1); }
+// Tile row of block i of pixel part q of rpw rows: a part's blocks are its rows
+// one after the other, each in two column halves.
+__device__ __forceinline__ constexpr int h2_row(int q, int rpw, int i) { return q * rpw + (i >> 1); }
 
 // s_waitcnt vmcnt(at most n) for a wave-uniform run-time n: the largest of a few
 // constants not above it.
@@ -759,11 +758,12 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
     constexpr int SPL = Tr<DT>::SPL;
     constexpr int KPL = SPL * SEG, KSTEP = 4 * KPL;
     constexpr int NBP = h2_nbp(NB), NG = NB / NBP, NQ = 4 / NG;
-    constexpr int TH = h2_th(NB), BLOCKS = TH * HT_W / 16, BPW = BLOCKS / NQ;
+    constexpr int TH = h2_th(NB), BLOCKS = TH * HT_W / 16, BPW = BLOCKS / NQ, RPW = BPW / 2;
     constexpr bool FIX = CPS > 0;
+    constexpr bool TAPS = FIX && CPS * SEG == KSTEP;  // a K step is one filter tap
     constexpr int KSM = FIX ? (9 * CPS * SEG + KSTEP - 1) / KSTEP : h2_ksmax(DT);
     constexpr int MAXBLK = FIX ? (h2_wslots(TH + 2, HT_W + 2, FIX ? CPS : 1) / 64 + 3) / 4 : H2_MAXBLK;
-    static_assert(NG * NBP == NB && (TH / 2) % NQ == 0, "wave split");
+    static_assert(NG * NBP == NB && RPW % 2 == 0 && RPW * NQ == TH, "wave split");
     extern __shared__ __align__(16) unsigned char halo_raw[];
     u32x4 *lds = reinterpret_cast<u32x4 *>(halo_raw);
 
@@ -893,14 +893,14 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
             // FIX: the LDS address for the wave's first block (constant offsets lead to the others)
             if constexpr (FIX)
                 toffb[ks][j] += (int)(unsigned)(size_t)(const __attribute__((address_space(3))) unsigned char *)halo_raw +
-                                (2 * wq * LW + lrow) * pst * 16;
+                                (h2_row(wq, RPW, 0) * LW + lrow) * pst * 16;
         }
-    // this wave's blocks: block i is tile row h2_row(wq, NQ, i), columns
+    // this wave's blocks: block i is tile row h2_row(wq, RPW, i), columns
     // 16 * (i & 1) + (0..15); lane lrow reads the A row of pixel lrow
     int pbb[BPW];
 #pragma unroll
     for (int i = 0; i < BPW; ++i)
-        pbb[i] = (h2_row(wq, NQ, i) * SD * LW + (16 * (i & 1) + lrow) * SD) * pst * 16;
+        pbb[i] = (h2_row(wq, RPW, i) * SD * LW + (16 * (i & 1) + lrow) * SD) * pst * 16;
     // pooled: a lane's accumulators are one channel of four pixels (pixels are
     // MFMA operand A); else four channels of one pixel (weights are operand A)
     constexpr int CH = POOL ? 1 : 4;
@@ -937,36 +937,62 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
         for (int i = 0; i < BPW; ++i)
 #pragma unroll
             for (int nb = 0; nb < NBP; ++nb) acc[i][nb] = f4{0.f, 0.f, 0.f, 0.f};
-        const unsigned char *wbuf = halo_raw + (size_t)cbuf * wslots * 16;
         const int woff = cbuf * wslots * 16;
-        const unsigned char *blk[BPW];
+        if constexpr (TAPS) {
+            // window row by window row: a fragment read once serves every
+            // output row whose filter covers it (up to three), and each output
+            // still adds its taps in order
+            using lds16 = const __attribute__((address_space(3))) u32x4;
+            const auto *q = (const __attribute__((address_space(3))) unsigned char *)(size_t)(unsigned)(toffb[0][0] + woff);
 #pragma unroll
-        for (int i = 0; i < BPW; ++i) blk[i] = wbuf + pbb[i];
+            for (int ir = 0; ir < RPW + 2; ++ir)
 #pragma unroll
-        for (int ks = 0; ks < KSM; ++ks) {
-            if (FIX || ks < KS) {
-                u32x4 af[BPW][SPL];
-                if constexpr (FIX) {
+                for (int sx = 0; sx < 3; ++sx)
 #pragma unroll
-                    for (int j = 0; j < SPL; ++j) {
-                        const auto *q = (const __attribute__((address_space(3))) unsigned char *)(size_t)(unsigned)(toffb[ks][j] + woff);
+                    for (int c = 0; c < 2; ++c) {
+                        const u32x4 f[1] = {*(lds16 *)(q + (ir * (HT_W + 2) + sx + 16 * c) * h2_pitch(FIX ? CPS : 1) * 16)};
+#pragma unroll
+                        for (int r = 0; r < 3; ++r) {
+                            const int row = ir - r;
+                            if (row < 0 || row >= RPW) continue;
+#pragma unroll
+                            for (int nb = 0; nb < NBP; ++nb) {
+                                if constexpr (POOL) mma<DT>(acc[2 * row + c][nb], f, wr[nb][3 * r + sx]);
+                                else mma<DT>(acc[2 * row + c][nb], wr[nb][3 * r + sx], f);
+                            }
+                        }
+                    }
+        } else {
+            const unsigned char *wbuf = halo_raw + woff;
+            const unsigned char *blk[BPW];
+#pragma unroll
+            for (int i = 0; i < BPW; ++i) blk[i] = wbuf + pbb[i];
+#pragma unroll
+            for (int ks = 0; ks < KSM; ++ks) {
+                if (FIX || ks < KS) {
+                    u32x4 af[BPW][SPL];
+                    if constexpr (FIX) {
+#pragma unroll
+                        for (int j = 0; j < SPL; ++j) {
+                            const auto *q = (const __attribute__((address_space(3))) unsigned char *)(size_t)(unsigned)(toffb[ks][j] + woff);
+#pragma unroll
+                            for (int i = 0; i < BPW; ++i)
+                                af[i][j] = *(const __attribute__((address_space(3))) u32x4 *)(q + ((i >> 1) * (HT_W + 2) + 16 * (i & 1)) * h2_pitch(FIX ? CPS : 1) * 16);
+                        }
+                    } else {
 #pragma unroll
                         for (int i = 0; i < BPW; ++i)
-                            af[i][j] = *(const __attribute__((address_space(3))) u32x4 *)(q + ((2 * NQ * (i >> 2) + ((i >> 1) & 1)) * (HT_W + 2) + 16 * (i & 1)) * h2_pitch(FIX ? CPS : 1) * 16);
+#pragma unroll
+                            for (int j = 0; j < SPL; ++j) af[i][j] = *reinterpret_cast<const u32x4 *>(blk[i] + toffb[ks][j]);
                     }
-                } else {
 #pragma unroll
                     for (int i = 0; i < BPW; ++i)
 #pragma unroll
-                        for (int j = 0; j < SPL; ++j) af[i][j] = *reinterpret_cast<const u32x4 *>(blk[i] + toffb[ks][j]);
+                        for (int nb = 0; nb < NBP; ++nb) {
+                            if constexpr (POOL) mma<DT>(acc[i][nb], af[i], wr[nb][ks]);
+                            else mma<DT>(acc[i][nb], wr[nb][ks], af[i]);
+                        }
                 }
-#pragma unroll
-                for (int i = 0; i < BPW; ++i)
-#pragma unroll
-                    for (int nb = 0; nb < NBP; ++nb) {
-                        if constexpr (POOL) mma<DT>(acc[i][nb], af[i], wr[nb][ks]);
-                        else mma<DT>(acc[i][nb], wr[nb][ks], af[i]);
-                    }
             }
         }
 
@@ -991,7 +1017,7 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
 #pragma unroll
                 for (int i = 0; i < BPW; ++i) {
                     if (i & 2) continue;
-                    const int hp = (th0 + h2_row(wq, NQ, i)) >> 1;
+                    const int hp = (th0 + h2_row(wq, RPW, i)) >> 1;
                     if (hp >= Hp) continue;  // wave-uniform
                     const int wpb = (tw0 + 16 * (i & 1)) >> 1;
                     const int soff = (hp * Wp + wpb) * a.cout_p;
@@ -1022,7 +1048,7 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
                 const int ch = (wg * NBP + nb) * 16 + 4 * lgrp;  // cout_p is a multiple of 4
 #pragma unroll
                 for (int i = 0; i < BPW; ++i) {
-                    const int ho = th0 + h2_row(wq, NQ, i);
+                    const int ho = th0 + h2_row(wq, RPW, i);
                     if (ho >= a.Ho) continue;  // wave-uniform
                     const int wob = tw0 + 16 * (i & 1);
                     const int soff = (ho * a.Wo + wob) * a.cout_p;
@@ -1116,7 +1142,7 @@ static hipError_t go_halo2(const ConvArgs &a, int grid, int nbuf, size_t lds, hi
 // 535 vector instructions a wave and tile besides the MFMAs, more than the
 // MFMAs take: tile positions divided out (150), window addresses (84), fragment
 // addresses (72).  64 images of 104 x 104 x 32 -> 64 channels, pooled: 38.5 us
-// before, 30 with these (floor 21: the MFMAs at the rate a probe reaches).
+// before, 30 with these, 28.4 with window rows read once (32 channels).
 template <int DT, bool POOL, bool AM>
 static hipError_t go_halo2(const ConvArgs &a, int grid, int nbuf, size_t lds, hipStream_t s)
 {
