@@ -743,6 +743,11 @@ __device__ __forceinline__ void wait_vm_upto(int n)
     }
 }
 
+template <int N>
+struct Int {
+    static constexpr int value = N;
+};
+
 // 16-byte units of a window buffer, rounded to whole 1 KB transfers.
 __host__ __device__ constexpr int h2_wslots(int lh, int lw, int cps) { return (lh * lw * h2_pitch(cps) + 63) / 64 * 64; }
 
@@ -938,30 +943,61 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
 #pragma unroll
             for (int nb = 0; nb < NBP; ++nb) acc[i][nb] = f4{0.f, 0.f, 0.f, 0.f};
         const int woff = cbuf * wslots * 16;
+        // the second column half of a tile at the right edge can lie outside
+        // altogether: no work for it (one block in eight at 104 columns)
+        const bool half = tw0 + 16 >= a.Wo;
         if constexpr (TAPS) {
             // window row by window row: a fragment read once serves every
             // output row whose filter covers it (up to three), and each output
             // still adds its taps in order
             using lds16 = const __attribute__((address_space(3))) u32x4;
             const auto *q = (const __attribute__((address_space(3))) unsigned char *)(size_t)(unsigned)(toffb[0][0] + woff);
+            auto taps = [&](auto halves) {
 #pragma unroll
-            for (int ir = 0; ir < RPW + 2; ++ir)
+                for (int ir = 0; ir < RPW + 2; ++ir)
 #pragma unroll
-                for (int sx = 0; sx < 3; ++sx)
+                    for (int sx = 0; sx < 3; ++sx)
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        const u32x4 f[1] = {*(lds16 *)(q + (ir * (HT_W + 2) + sx + 16 * c) * h2_pitch(FIX ? CPS : 1) * 16)};
+                        for (int c = 0; c < halves.value; ++c) {
+                            const u32x4 f[1] = {*(lds16 *)(q + (ir * (HT_W + 2) + sx + 16 * c) * h2_pitch(FIX ? CPS : 1) * 16)};
 #pragma unroll
-                        for (int r = 0; r < 3; ++r) {
-                            const int row = ir - r;
-                            if (row < 0 || row >= RPW) continue;
+                            for (int r = 0; r < 3; ++r) {
+                                const int row = ir - r;
+                                if (row < 0 || row >= RPW) continue;
 #pragma unroll
-                            for (int nb = 0; nb < NBP; ++nb) {
-                                if constexpr (POOL) mma<DT>(acc[2 * row + c][nb], f, wr[nb][3 * r + sx]);
-                                else mma<DT>(acc[2 * row + c][nb], wr[nb][3 * r + sx], f);
+                                for (int nb = 0; nb < NBP; ++nb) {
+                                    if constexpr (POOL) mma<DT>(acc[2 * row + c][nb], f, wr[nb][3 * r + sx]);
+                                    else mma<DT>(acc[2 * row + c][nb], wr[nb][3 * r + sx], f);
+                                }
                             }
                         }
+            };
+            if (half) taps(Int<1>());
+            else taps(Int<2>());
+        } else if constexpr (FIX) {
+            auto steps = [&](auto halves) {
+                constexpr int ST = 3 - halves.value;  // every block, or the first column halves
+#pragma unroll
+                for (int ks = 0; ks < KSM; ++ks) {
+                    u32x4 af[BPW][SPL];
+#pragma unroll
+                    for (int j = 0; j < SPL; ++j) {
+                        const auto *q = (const __attribute__((address_space(3))) unsigned char *)(size_t)(unsigned)(toffb[ks][j] + woff);
+#pragma unroll
+                        for (int i = 0; i < BPW; i += ST)
+                            af[i][j] = *(const __attribute__((address_space(3))) u32x4 *)(q + ((i >> 1) * (HT_W + 2) + 16 * (i & 1)) * h2_pitch(FIX ? CPS : 1) * 16);
                     }
+#pragma unroll
+                    for (int i = 0; i < BPW; i += ST)
+#pragma unroll
+                        for (int nb = 0; nb < NBP; ++nb) {
+                            if constexpr (POOL) mma<DT>(acc[i][nb], af[i], wr[nb][ks]);
+                            else mma<DT>(acc[i][nb], wr[nb][ks], af[i]);
+                        }
+                }
+            };
+            if (half) steps(Int<1>());
+            else steps(Int<2>());
         } else {
             const unsigned char *wbuf = halo_raw + woff;
             const unsigned char *blk[BPW];
@@ -969,22 +1005,12 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
             for (int i = 0; i < BPW; ++i) blk[i] = wbuf + pbb[i];
 #pragma unroll
             for (int ks = 0; ks < KSM; ++ks) {
-                if (FIX || ks < KS) {
+                if (ks < KS) {
                     u32x4 af[BPW][SPL];
-                    if constexpr (FIX) {
 #pragma unroll
-                        for (int j = 0; j < SPL; ++j) {
-                            const auto *q = (const __attribute__((address_space(3))) unsigned char *)(size_t)(unsigned)(toffb[ks][j] + woff);
+                    for (int i = 0; i < BPW; ++i)
 #pragma unroll
-                            for (int i = 0; i < BPW; ++i)
-                                af[i][j] = *(const __attribute__((address_space(3))) u32x4 *)(q + ((i >> 1) * (HT_W + 2) + 16 * (i & 1)) * h2_pitch(FIX ? CPS : 1) * 16);
-                        }
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < BPW; ++i)
-#pragma unroll
-                            for (int j = 0; j < SPL; ++j) af[i][j] = *reinterpret_cast<const u32x4 *>(blk[i] + toffb[ks][j]);
-                    }
+                        for (int j = 0; j < SPL; ++j) af[i][j] = *reinterpret_cast<const u32x4 *>(blk[i] + toffb[ks][j]);
 #pragma unroll
                     for (int i = 0; i < BPW; ++i)
 #pragma unroll
@@ -1017,6 +1043,7 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
 #pragma unroll
                 for (int i = 0; i < BPW; ++i) {
                     if (i & 2) continue;
+                    if ((i & 1) && half) continue;  // wave-uniform
                     const int hp = (th0 + h2_row(wq, RPW, i)) >> 1;
                     if (hp >= Hp) continue;  // wave-uniform
                     const int wpb = (tw0 + 16 * (i & 1)) >> 1;
@@ -1049,7 +1076,7 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
 #pragma unroll
                 for (int i = 0; i < BPW; ++i) {
                     const int ho = th0 + h2_row(wq, RPW, i);
-                    if (ho >= a.Ho) continue;  // wave-uniform
+                    if (ho >= a.Ho || ((i & 1) && half)) continue;  // wave-uniform
                     const int wob = tw0 + 16 * (i & 1);
                     const int soff = (ho * a.Wo + wob) * a.cout_p;
                     const bool ok = wob + lrow < a.Wo && ch < a.cout_p;
@@ -1142,7 +1169,8 @@ static hipError_t go_halo2(const ConvArgs &a, int grid, int nbuf, size_t lds, hi
 // 535 vector instructions a wave and tile besides the MFMAs, more than the
 // MFMAs take: tile positions divided out (150), window addresses (84), fragment
 // addresses (72).  64 images of 104 x 104 x 32 -> 64 channels, pooled: 38.5 us
-// before, 30 with these, 28.4 with window rows read once (32 channels).
+// before, 30 with these, 28.4 with window rows read once (32 channels), 28.1 with
+// the empty column halves left out.
 template <int DT, bool POOL, bool AM>
 static hipError_t go_halo2(const ConvArgs &a, int grid, int nbuf, size_t lds, hipStream_t s)
 {
