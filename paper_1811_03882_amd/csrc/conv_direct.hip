@@ -1114,42 +1114,66 @@ __global__ void __launch_bounds__(256, 2) conv_halo2(ConvArgs a, int nbuf)
     }
 }
 
-// Window slots (16 bytes) of one LDS buffer of the persistent halo kernel.
-static int halo2_wslots(int dt, const ConvArgs &a)
-{
-    const int cps = a.cin_p / seg_el(dt);
-    const int th = h2_th((a.cout_p + 15) / 16);
-    const int lh = (th - 1) * a.stride + a.R, lw = (HT_W - 1) * a.stride + a.S;
-    return h2_wslots(lh, lw, cps);
-}
-
 constexpr size_t H2_LDS_MAX = 76 * 1024;  // two workgroups per CU
 
-// Window buffers: as many as fit (up to 4), at least 2.
-static int halo2_nbuf(int dt, const ConvArgs &a)
+// Window slots (16 bytes) of one LDS buffer of the persistent halo kernel at
+// the tile of nb 16-channel blocks.
+static int halo2_wslots(int dt, const ConvArgs &a, int nb)
 {
-    const size_t per = (size_t)halo2_wslots(dt, a) * 16;
+    const int th = h2_th(nb);
+    const int lh = (th - 1) * a.stride + a.R, lw = (HT_W - 1) * a.stride + a.S;
+    return h2_wslots(lh, lw, a.cin_p / seg_el(dt));
+}
+
+// The 16-channel blocks a layer runs with: its own, or four, the last ones
+// empty, in BF16 with three blocks or where two windows of the 16-row tiles do
+// not fit.
+static int halo2_blocks(int dt, const ConvArgs &a)
+{
+    const int nb = (a.cout_p + 15) / 16;
+    const bool four = dt == BF16 && (nb == 3 || (nb < 3 && 2 * (size_t)halo2_wslots(dt, a, nb) * 16 > H2_LDS_MAX));
+    return four ? 4 : nb;
+}
+
+// Window buffers: as many as fit (up to 4), at least 2.
+static int halo2_nbuf(size_t per)
+{
     int nb = 4;
     while (nb > 2 && nb * per > H2_LDS_MAX) --nb;
     return nb;
 }
 
-bool halo2_ok(int dt, const ConvArgs &a)
+bool halo2_ok(int dt, const ConvArgs &a, bool as_four)
 {
     const int kstep = dt == FP8 ? 128 : (dt == BF16 ? 32 : 16);
     const int K = a.R * a.S * a.cin_p;
-    const int ws = halo2_wslots(dt, a);
-    const int nb = (a.cout_p + 15) / 16;
+    const int nb = as_four ? halo2_blocks(dt, a) : (a.cout_p + 15) / 16;
+    const int ws = halo2_wslots(dt, a, nb);
     return kblock_ch(dt, a.cin_p, a.R * a.S) == a.cin_p && nb <= 4 && nb != 3 && (K + kstep - 1) / kstep <= h2_ksmax(dt) &&
            a.stride <= 2 && (size_t)a.Ho * a.Wo * a.cout_p * esize(dt) < (1u << 31) &&
            (size_t)a.H * a.W * a.cin_p * esize(dt) < (1u << 31) && ws / 64 <= 4 * H2_MAXBLK &&
            2 * (size_t)ws * 16 <= H2_LDS_MAX;
 }
 
+// The instance for a shape: CPS of those with the window's layout built in, or 0.
+static int halo2_fix(int dt, const ConvArgs &a)
+{
+    const bool fix = dt == BF16 && a.R == 3 && a.S == 3 && a.stride == 1 &&
+                     (size_t)(a.H + 64) * a.W * a.cin_p * esize(dt) < (1u << 30);
+    return fix && (a.cin_p == 16 || a.cin_p == 32) ? a.cin_p / seg_el(BF16) : 0;
+}
+
+long halo2_tiles(int dt, const ConvArgs &a, bool *fixed)
+{
+    const int th = h2_th(halo2_blocks(dt, a));
+    if (fixed) *fixed = halo2_fix(dt, a) != 0;
+    return (long)a.batch * ((a.Ho + th - 1) / th) * ((a.Wo + HT_W - 1) / HT_W);
+}
+
 template <int DT, bool POOL, bool AM, int CPS>
 static hipError_t go_halo2(const ConvArgs &a, int grid, int nbuf, size_t lds, hipStream_t s)
 {
-    const int nb = (a.cout_p + 15) / 16;
+    const int nb = halo2_blocks(DT, a);
     if constexpr (CPS != 4) {  // two windows of 18 x 34 pixels of 4 chunks are past H2_LDS_MAX
         switch (nb) {
         case 1: allow_lds(conv_halo2<DT, POOL, 1, AM, CPS>, lds); hipLaunchKernelGGL((conv_halo2<DT, POOL, 1, AM, CPS>), dim3(grid), dim3(256), lds, s, a, nbuf); return hipGetLastError();
@@ -1175,10 +1199,9 @@ template <int DT, bool POOL, bool AM>
 static hipError_t go_halo2(const ConvArgs &a, int grid, int nbuf, size_t lds, hipStream_t s)
 {
     if constexpr (DT == BF16) {
-        if (a.R == 3 && a.S == 3 && a.stride == 1 && (size_t)(a.H + 64) * a.W * a.cin_p * esize(DT) < (1u << 30)) {
-            if (a.cin_p == 16) return go_halo2<DT, POOL, AM, 2>(a, grid, nbuf, lds, s);
-            if (a.cin_p == 32) return go_halo2<DT, POOL, AM, 4>(a, grid, nbuf, lds, s);
-        }
+        const int cps = halo2_fix(DT, a);
+        if (cps == 2) return go_halo2<DT, POOL, AM, 2>(a, grid, nbuf, lds, s);
+        if (cps == 4) return go_halo2<DT, POOL, AM, 4>(a, grid, nbuf, lds, s);
     }
     return go_halo2<DT, POOL, AM, 0>(a, grid, nbuf, lds, s);
 }
@@ -1194,11 +1217,11 @@ static hipError_t go_halo2_dt(const ConvArgs &a, int grid, int nbuf, size_t lds,
 
 hipError_t launch_conv_halo2(int dt, const ConvArgs &a, hipStream_t s)
 {
-    if (!halo2_ok(dt, a)) return hipErrorInvalidValue;
-    const int th = h2_th((a.cout_p + 15) / 16);
-    const long tiles = (long)a.batch * ((a.Ho + th - 1) / th) * ((a.Wo + HT_W - 1) / HT_W);
-    const int nbuf = halo2_nbuf(dt, a);
-    const size_t lds = (size_t)nbuf * halo2_wslots(dt, a) * 16;
+    if (!halo2_ok(dt, a, true)) return hipErrorInvalidValue;
+    const long tiles = halo2_tiles(dt, a, nullptr);
+    const size_t per = (size_t)halo2_wslots(dt, a, halo2_blocks(dt, a)) * 16;
+    const int nbuf = halo2_nbuf(per);
+    const size_t lds = nbuf * per;
     // two workgroups per CU, a multiple of 8 (the tile runs are per XCD)
     const long want = std::min<long>(tiles, 512L);
     const int grid = (int)std::max<long>(8, (want + 7) / 8 * 8);

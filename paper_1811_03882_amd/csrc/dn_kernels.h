@@ -109,7 +109,11 @@ hipError_t launch_conv_halo(int dt, const ConvArgs &a, hipStream_t s);
 // The persistent halo kernel (weights in registers, double-buffered windows,
 // same reduction order): launch_conv(dt, HALO2_TILE, ...) when halo2_ok().
 constexpr int HALO2_TILE = 101;
-bool halo2_ok(int dt, const ConvArgs &a);
+// as_four: also the BF16 layers of one to three 16-channel blocks that only run
+// as four (three blocks; or a window too large for the tiles of one and two).
+bool halo2_ok(int dt, const ConvArgs &a, bool as_four = false);
+// Output tiles, and whether the instance with its window's layout built in takes it.
+long halo2_tiles(int dt, const ConvArgs &a, bool *fixed);
 hipError_t launch_conv_halo2(int dt, const ConvArgs &a, hipStream_t s);
 
 // The pipelined GEMM kernel (conv_pipe.hip): tiles PIPE_TILE .. + PIPE_TILES - 1

@@ -2102,11 +2102,24 @@ static dn_status conv_geometry(const dn_conv_desc *d, ConvArgs *a, int *tile, in
         ConvArgs g{};
         g.batch = d->batch; g.H = d->in_h; g.W = d->in_w; g.Ho = Ho; g.Wo = Wo;
         g.R = g.S = d->ksize; g.stride = d->stride; g.pad = d->pad; g.cin_p = cin_p; g.cout_p = cout_p; g.k_pad = k_pad;
-        if (sp <= 0 && halo2_ok(dt, g)) {
-            // small K: the persistent halo kernel reads every input pixel once
-            // (104x104x32 -> 64 + pool, batch 64, BF16: 69 us on a GEMM tile)
+        // The persistent halo kernel for small K reads every input pixel once
+        // (BF16 + pool: 104x104x32 -> 64, batch 64: 69 us on a GEMM tile, 28
+        // here; 100x100x32 -> 48, batch 34: 36 us, 17 here).  Its tiles for
+        // four channel blocks lose where they leave CUs without one (56x56x32
+        // -> 64, batch 4, 56 tiles: 7.3 us on a GEMM tile, 7.6 here), and in
+        // the general form, which 24 channels take, below two a CU (80x80,
+        // batch 12, 360 tiles: 11.1 and 11.2; 1768 tiles: 33 and 22).
+        bool halo = sp <= 0 && halo2_ok(dt, g, true);
+        if (halo && dt == BF16 && (cout_p > 32 || !halo2_ok(dt, g))) {
+            bool fixed;
+            halo = halo2_tiles(dt, g, &fixed) >= (fixed ? 256 : 512);
+        }
+        // one or two K-tiles on less than a tile a CU: no pipeline to fill
+        // (8x8x128 -> 256 1x1, batch 12: 7.5 us register-staged, 7.75 pipelined)
+        const bool brief = nkt <= 2 && (long)((M + 63) / 64) * ((cout_p + 63) / 64) < 256;
+        if (halo) {
             t = HALO2_TILE;
-        } else if (pipe_ok(dt, g)) {
+        } else if (!brief && pipe_ok(dt, g)) {
             // here a split costs a second launch (the workspace has no zeroed
             // counters for the in-kernel finish): split only where that pays
             if (sp <= 0) {
@@ -2129,7 +2142,7 @@ static dn_status conv_geometry(const dn_conv_desc *d, ConvArgs *a, int *tile, in
         ConvArgs h{};
         h.R = h.S = d->ksize; h.stride = d->stride; h.pad = d->pad; h.cin_p = cin_p; h.cout_p = cout_p; h.k_pad = k_pad;
         h.H = d->in_h; h.W = d->in_w; h.Ho = Ho; h.Wo = Wo;
-        if (t == HALO_TILE ? !halo_ok(dt, h) : !halo2_ok(dt, h))
+        if (t == HALO_TILE ? !halo_ok(dt, h) : !halo2_ok(dt, h, d->tile < 0))
             return fail(DN_EUNSUPPORTED, "conv desc: this shape cannot use the halo kernel %d", t);
     }
     if (a) {
