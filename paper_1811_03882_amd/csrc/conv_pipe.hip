@@ -79,26 +79,39 @@ __device__ __forceinline__ void pipe_epilogue(const ConvArgs &a, f4 (&acc)[FM][F
         }
         return;
     }
+    float bi[FN][4], scl[FN][4];
 #pragma unroll
     for (int fn = 0; fn < FN; ++fn) {
         const int col = colb + fn * 16;
-        if (col >= a.cout_p) continue;
-        const float4 bias = *reinterpret_cast<const float4 *>(a.bias + col);
-        const float bi[4] = {bias.x, bias.y, bias.z, bias.w};
-        float scl[4] = {1.0f, 1.0f, 1.0f, 1.0f};
-        if constexpr (DT == FP8) {
-            const float4 ws = *reinterpret_cast<const float4 *>(a.wscale + col);
-            scl[0] = ws.x * a.in_scale; scl[1] = ws.y * a.in_scale; scl[2] = ws.z * a.in_scale; scl[3] = ws.w * a.in_scale;
-        }
+        const bool ok = col < a.cout_p;
+        const float4 bias = ok ? *reinterpret_cast<const float4 *>(a.bias + col) : float4{0.f, 0.f, 0.f, 0.f};
+        bi[fn][0] = bias.x; bi[fn][1] = bias.y; bi[fn][2] = bias.z; bi[fn][3] = bias.w;
 #pragma unroll
-        for (int fm = 0; fm < FM; ++fm) {
-            const int m = rowb + fm * 16;
-            if (m >= a.M) continue;
+        for (int i = 0; i < 4; ++i) scl[fn][i] = 1.0f;
+        if constexpr (DT == FP8) {
+            const float4 ws = ok ? *reinterpret_cast<const float4 *>(a.wscale + col) : float4{0.f, 0.f, 0.f, 0.f};
+            scl[fn][0] = ws.x * a.in_scale; scl[fn][1] = ws.y * a.in_scale; scl[fn][2] = ws.z * a.in_scale; scl[fn][3] = ws.w * a.in_scale;
+        }
+    }
+    // Pixel by pixel, so that the stores to one cache line follow each other:
+    // every workgroup of a wide layer ends at once, and with the channel blocks
+    // outermost the counters showed 2.4 times the output's bytes written (54 MB
+    // for 22 at 13x13x1024, batch 64; 22 in this order, and 3 % off the layer's
+    // time; FP8 13x13x512 -> 1024, batch 32: 34.1 -> 32.8 us).
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm) {
+        const int m = rowb + fm * 16;
+        if (m >= a.M) continue;
+        unsigned c01[FN], c23[FN];  // BF16 pairs
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn) {
+            const int col = colb + fn * 16;
+            const bool ok = col < a.cout_p;
             const size_t o = (size_t)m * a.cout_p + col;
             float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = activate(acc[fm][fn][i] * scl[i] + bi[i], a.act, a.slope);
-            if (a.res) {
+            for (int i = 0; i < 4; ++i) v[i] = activate(acc[fm][fn][i] * scl[fn][i] + bi[fn][i], a.act, a.slope);
+            if (a.res && ok) {
                 float r[4];
                 load4<DT>(a.res, o, r);
 #pragma unroll
@@ -106,8 +119,26 @@ __device__ __forceinline__ void pipe_epilogue(const ConvArgs &a, f4 (&acc)[FM][F
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] *= a.out_inv_scale;
-            if (a.nchw) store4_nchw<DT>(a.nchw, a.nchw_c, a.Ho * a.Wo, a.nchw_scale, (unsigned)m, col, v);
-            else store4<DT>(a.y, o, v);
+            if (a.nchw) {
+                if (ok) store4_nchw<DT>(a.nchw, a.nchw_c, a.Ho * a.Wo, a.nchw_scale, (unsigned)m, col, v);
+            } else if constexpr (DT == BF16 && FN % 2 == 0) {
+                c01[fn] = (unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16);
+                c23[fn] = (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16);
+                if (fn & 1) {
+                    // lanes of the first and third 16 take their neighbours' (the
+                    // next 16 lanes') four channels of block fn - 1, those give
+                    // theirs of block fn for them: eight channels a lane, one store
+                    const auto lo = __builtin_amdgcn_permlane16_swap(c01[fn - 1], c01[fn], false, false);
+                    const auto hi = __builtin_amdgcn_permlane16_swap(c23[fn - 1], c23[fn], false, false);
+                    const int g = (threadIdx.x >> 4) & 3;
+                    const int col8 = colb - 4 * g + (fn - 1 + (g & 1)) * 16 + (g >> 1) * 8;
+                    if (col8 < a.cout_p)  // cout_p is a multiple of 8
+                        *reinterpret_cast<u32x4 *>(reinterpret_cast<unsigned char *>(a.y) + ((size_t)m * a.cout_p + col8) * 2) =
+                            u32x4{lo[0], hi[0], lo[1], hi[1]};
+                }
+            } else if (ok) {
+                store4<DT>(a.y, o, v);
+            }
         }
     }
 }
