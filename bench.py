@@ -287,17 +287,17 @@ def traffic_from_profiles(layer_key: str, tile: int):
     PMC summary, only if it was taken on the current kernel source and with
     the tile configuration this run chose (the autotuner may pick either of
     two near-equal tiles from run to run; the summary holds one entry each)."""
-    path = os.path.join(ROOT, "profiles", "conv_dominant_b64_bf16_hbm_traffic.json")
-    if not os.path.exists(path):
-        return None
-    try:
-        with open(path) as f:
-            d = json.load(f)
-        if d.get("kernel_source_hash") != kernel_source_hash():
-            return None
-        return d.get(layer_key, {}).get("tile%d" % tile, {}).get("hbm_bytes_per_launch")
-    except (OSError, ValueError):
-        return None
+    # one file per tile family: the two-stage tiles, the pipelined ones
+    for name in ("conv_dominant_b64_bf16_hbm_traffic.json", "conv_dominant_b64_bf16_hbm_traffic_pipe.json"):
+        try:
+            with open(os.path.join(ROOT, "profiles", name)) as f:
+                d = json.load(f)
+        except (OSError, ValueError):
+            continue
+        got = d.get(layer_key, {}).get("tile%d" % tile, {}).get("hbm_bytes_per_launch")
+        if d.get("kernel_source_hash") == kernel_source_hash() and got:
+            return got
+    return None
 
 
 def _csv_rows(path):
