@@ -143,6 +143,37 @@ __device__ __forceinline__ void pipe_epilogue(const ConvArgs &a, f4 (&acc)[FM][F
     }
 }
 
+// The pooled tiles' unsplit epilogue: a lane's four accumulators are the window
+// of one channel, as in conv_epilogue, but window by window, so that the stores
+// to one cache line follow each other here too (nine-layer net, BF16, batch 64,
+// with two such layers: 519 -> 510 us).
+template <int DT, int FM, int FN>
+__device__ __forceinline__ void pipe_epilogue_pool(const ConvArgs &a, f4 (&acc)[FM][FN], int rowb, int colb)
+{
+    float bias[FN], scl[FN];
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) {
+        const int col = colb + fn * 16;
+        bias[fn] = col < a.cout_p ? a.bias[col] : 0.0f;
+        scl[fn] = (DT == FP8 && col < a.cout_p) ? a.wscale[col] * a.in_scale : 1.0f;
+    }
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm) {
+        const int mb = rowb + fm * 16;
+        if (mb >= a.M) continue;
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn) {
+            const int col = colb + fn * 16;
+            if (col >= a.cout_p) continue;
+            const float w4[4] = {acc[fm][fn][0], acc[fm][fn][1], acc[fm][fn][2], acc[fm][fn][3]};
+            const float mx = fmaxf(fmaxf(w4[0], w4[1]), fmaxf(w4[2], w4[3]));
+            const size_t o = (size_t)(mb >> 2) * a.cout_p + col;
+            store_el<DT>(a.y, o, activate(mx * scl[fn] + bias[fn], a.act, a.slope) * a.out_inv_scale);
+            if (a.argmax) a.argmax[o] = window_argmax<DT>(w4, scl[fn], bias[fn], a.act, a.slope, a.out_inv_scale);
+        }
+    }
+}
+
 // s_waitcnt vmcnt(N) lgkmcnt(0), expcnt left at its maximum (no wait)
 template <int N> __device__ __forceinline__ void wait_vm_lgkm0()
 {
@@ -374,8 +405,10 @@ __global__ void __launch_bounds__(64 * WM * WN, WPE) conv_pipe(ConvArgs a)
     }
     __syncthreads();
 
-    if constexpr (POOL) conv_epilogue<DT, FM, FN>(a, acc, m0 + wm * WTM + 4 * lgrp, n0 + wn * WTN + lrow);
-    else pipe_epilogue<DT, FM, FN>(a, acc, m0 + wm * WTM + lrow, n0 + wn * WTN + 4 * lgrp);
+    if constexpr (POOL) {
+        if (a.splits > 1) conv_epilogue<DT, FM, FN>(a, acc, m0 + wm * WTM + 4 * lgrp, n0 + wn * WTN + lrow);
+        else pipe_epilogue_pool<DT, FM, FN>(a, acc, m0 + wm * WTM + 4 * lgrp, n0 + wn * WTN + lrow);
+    } else pipe_epilogue<DT, FM, FN>(a, acc, m0 + wm * WTM + lrow, n0 + wn * WTN + 4 * lgrp);
     if (a.splits > 1 && a.tile_count) splitk_tail<DT, BM, BN, 64 * NW>(a, m0, n0, sA);
 }
 
