@@ -150,7 +150,8 @@ __global__ void __launch_bounds__(256) conv_first(FirstArgs a)
         else stage(std::false_type{});
     }
 
-    for (int i = blockIdx.x * 256 + tid; i < a.nzero; i += gridDim.x * 256) a.zero[i] = 0u;
+    // (64-bit indices: blocks x 256 threads pass 2^31 with 8.4 M small images)
+    for (size_t i = (size_t)blockIdx.x * 256 + tid; i < (size_t)a.nzero; i += (size_t)gridDim.x * 256) a.zero[i] = 0u;
 
     // 16 zero bytes after the window: read units past row R or tap S read here
     const int zaddr = (LH * LW * PIXB + 15) & ~15;
