@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "jacobi_plan.h"
+
 namespace dnk {
 
 enum { F32 = 0, BF16 = 1, FP8 = 2 };
@@ -222,11 +224,9 @@ hipError_t detect_scratch(void **ptr);
 // largest interior change.
 hipError_t launch_jacobi_step(const double *u, double *v, int n, int m, unsigned long long *max_change, hipStream_t s);
 // The same bits as t steps in one launch of the tiled kernel; rows: rows per
-// wave, 4 / 8 / 12 / 16.  jacobi_plan() picks them and the number of launches
-// (their t differ by at most one).  in_place: the grid fits in one workgroup's
-// patch, u == v is allowed; otherwise u and v are different buffers.
-struct JacobiPlan { int rows, launches; bool in_place; };
-JacobiPlan jacobi_plan(int n, int m, int iters);
+// wave, 4 / 8 / 12 / 16.  jacobi_plan() (jacobi_plan.h) picks them and the
+// number of launches (their t differ by at most one).  in_place: the grid fits in
+// one workgroup's patch, u == v is allowed; otherwise u and v are different buffers.
 hipError_t launch_jacobi_tile(int rows, const double *u, double *v, int n, int m, int t, unsigned long long *max_change, hipStream_t s);
 
 // MFMA-only throughput probe (measurement): blocks x 256 threads, out holds

@@ -1,0 +1,63 @@
+// How dn_jacobi splits its iterations over launches of the tiled kernel
+// (jacobi.hip).  Plain host C++.  Internal to the library.
+#pragma once
+
+namespace dnk {
+
+constexpr int JT_W = 8, JT_COLS = 128;  // waves of a patch, its columns
+
+struct JacobiPlan { int rows, launches; bool in_place; };
+
+// Workgroups of a patch height and iterations per launch; 0 if the rim leaves
+// nothing to write.
+inline long jacobi_groups(int n, int m, int rows, int t)
+{
+    const int wx = m <= JT_COLS ? JT_COLS : JT_COLS - 2 * t, wy = n <= rows ? rows : rows - 2 * t;
+    if (wx <= 0 || wy <= 0) return 0;
+    return ((long)(m + wx - 1) / wx) * ((n + wy - 1) / wy);
+}
+
+// Rows per wave and launches for `iters` iterations: the least launches x
+// (launch + t x iteration) over patch heights and iterations per launch t.  A
+// launch costs about 6.5 us with its loads and stores; an iteration 0.15 us of
+// barrier and LDS latency and, per workgroup a CU runs at once, 96 clocks of
+// issue a row (two waves on each SIMD, 12 instructions for two columns).  At
+// 1000x1500 the rule takes 96-row patches and 16 iterations: 256 workgroups.
+// A grid that fits in one patch needs no rim and no partner buffer: one launch,
+// in place (at most 4096 iterations each, so that a launch stays short).
+inline JacobiPlan jacobi_plan(int n, int m, int iters)
+{
+    JacobiPlan best{0, 0, false};
+    double cost = 1e300;
+    for (int r = 4; r <= 16; r += 4) {
+        const int rows = r * JT_W;
+        if (n <= rows && m <= JT_COLS) return JacobiPlan{r, (iters + 4095) / 4096, true};
+        for (int t = 1; t <= 24 && t <= iters; ++t) {
+            const long g = jacobi_groups(n, m, rows, t);
+            if (g == 0) break;
+            if (n > rows && (n - 1) / (rows - 2 * t) >= 65535) break;  // the launch's grid limit
+            // an even number of launches ends in the buffer it began in; an odd
+            // one (a single launch, or one for each of an odd number of
+            // iterations, where none is left for another) is followed by a copy
+            long launches = ((long)iters + t - 1) / t;
+            if (launches > 1 && launches < iters) launches += launches & 1;
+            const double copy = launches == 1 ? 6.5 : (launches & 1) ? 6.5 + 3.2e-6 * n * m : 0.0;
+            const double per_cu = (double)((g + 255) / 256);
+            const double us = launches * (6.5 + (double)iters / launches * (0.15 + 0.0457 * r * per_cu)) + copy;
+            if (us < cost) {
+                cost = us;
+                best = JacobiPlan{r, (int)launches, false};
+            }
+        }
+    }
+    return best;
+}
+
+// Iterations of launch k of the plan, `done` of `iters` before it: equal shares,
+// the larger ones first.
+inline int jacobi_share(const JacobiPlan &p, int iters, int done, int k)
+{
+    return (iters - done + (p.launches - k) - 1) / (p.launches - k);
+}
+
+}  // namespace dnk

@@ -1872,7 +1872,7 @@ extern "C" dn_status dn_jacobi(double *u, double *work, int n, int m, int iters,
     if (n < (1 << 19)) {
         const JacobiPlan p = jacobi_plan(n, m, iters);
         for (int k = 0, it = 0; k < p.launches; ++k) {
-            const int t = (iters - it + (p.launches - k) - 1) / (p.launches - k);
+            const int t = jacobi_share(p, iters, it, k);
             it += t;
             HIPCHK(launch_jacobi_tile(p.rows, a, p.in_place ? a : b, n, m, t, it == iters ? mc : nullptr, s));
             if (!p.in_place) std::swap(a, b);
