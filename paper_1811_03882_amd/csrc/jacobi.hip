@@ -18,7 +18,7 @@
 namespace dnk {
 
 // one iteration per launch (the per-iteration transfer mode, and grids too tall
-// for the tiled kernel's launch below)
+// or too wide for the tiled kernel's launch below)
 constexpr int JAC_BX = 64, JAC_BY = 4, JAC_STRIP = 8;
 
 __global__ void __launch_bounds__(JAC_BX * JAC_BY) jacobi_step(const double *__restrict__ u, double *__restrict__ v,
@@ -207,7 +207,7 @@ static hipError_t go_jacobi(const double *u, double *v, int n, int m, int t, uns
     if (t < 1 || 2 * hx >= JT_COLS || 2 * hy >= ROWS) return hipErrorInvalidValue;
     const long gx = hx ? ((long)m + JT_COLS - 2 * hx - 1) / (JT_COLS - 2 * hx) : 1;
     const long gy = hy ? ((long)n + ROWS - 2 * hy - 1) / (ROWS - 2 * hy) : 1;
-    if (gy > 65535 || (u == v && gx * gy > 1)) return hipErrorInvalidValue;
+    if (gy > JT_MAX_Y || gx > JT_MAX_X || (u == v && gx * gy > 1)) return hipErrorInvalidValue;
     if (max_change) hipLaunchKernelGGL(jacobi_zero, dim3(1), dim3(1), 0, s, max_change);
     hipLaunchKernelGGL(jacobi_tile<R>, dim3((unsigned)gx, (unsigned)gy), dim3(64 * JT_W), 0, s, u, v, n, m, t, hx, hy, max_change);
     return hipGetLastError();

@@ -17,6 +17,11 @@ inline long jacobi_groups(int n, int m, int rows, int t)
     return ((long)(m + wx - 1) / wx) * ((n + wy - 1) / wy);
 }
 
+// Limits of a launch: 65535 workgroups down, fewer than 2^32 threads across.
+constexpr int JT_MAX_Y = 65535, JT_MAX_X = (1 << 23) - 1;
+// Grids the tiled kernel takes with a rim of one: jacobi_plan() finds a plan.
+inline bool jacobi_tiled(int n, int m) { return n < (1 << 19) && m <= (JT_COLS - 2) * JT_MAX_X; }
+
 // Rows per wave and launches for `iters` iterations: the least launches x
 // (launch + t x iteration) over patch heights and iterations per launch t.  A
 // launch costs about 6.5 us with its loads and stores; an iteration 0.15 us of
@@ -35,7 +40,8 @@ inline JacobiPlan jacobi_plan(int n, int m, int iters)
         for (int t = 1; t <= 24 && t <= iters; ++t) {
             const long g = jacobi_groups(n, m, rows, t);
             if (g == 0) break;
-            if (n > rows && (n - 1) / (rows - 2 * t) >= 65535) break;  // the launch's grid limit
+            if (n > rows && (n - 1) / (rows - 2 * t) >= JT_MAX_Y) break;
+            if (m > JT_COLS && (m - 1) / (JT_COLS - 2 * t) >= JT_MAX_X) break;
             // an even number of launches ends in the buffer it began in; an odd
             // one (a single launch, or one for each of an odd number of
             // iterations, where none is left for another) is followed by a copy

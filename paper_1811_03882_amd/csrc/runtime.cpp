@@ -1869,7 +1869,7 @@ extern "C" dn_status dn_jacobi(double *u, double *work, int n, int m, int iters,
     }
     unsigned long long *mc = (unsigned long long *)max_change;
     double *a = u, *b = work;
-    if (n < (1 << 19)) {
+    if (jacobi_tiled(n, m)) {
         const JacobiPlan p = jacobi_plan(n, m, iters);
         for (int k = 0, it = 0; k < p.launches; ++k) {
             const int t = jacobi_share(p, iters, it, k);
@@ -1877,7 +1877,7 @@ extern "C" dn_status dn_jacobi(double *u, double *work, int n, int m, int iters,
             HIPCHK(launch_jacobi_tile(p.rows, a, p.in_place ? a : b, n, m, t, it == iters ? mc : nullptr, s));
             if (!p.in_place) std::swap(a, b);
         }
-    } else {  // taller than the tiled launch's grid
+    } else {  // taller or wider than the tiled launch's grid
         for (int it = 0; it < iters; ++it) {
             HIPCHK(launch_jacobi_step(a, b, n, m, it + 1 == iters ? mc : nullptr, s));
             std::swap(a, b);

@@ -27,7 +27,8 @@ static bool check(int n, int m, int iters)
         if (!ok) break;
         const long gx = hx ? ((long)m + JT_COLS - 2 * hx - 1) / (JT_COLS - 2 * hx) : 1;
         const long gy = hy ? ((long)n + rows - 2 * hy - 1) / (rows - 2 * hy) : 1;
-        ok = gy <= 65535 && (!p.in_place || gx * gy == 1);
+        // HIP's limits: 65535 blocks down, fewer than 2^32 threads across
+        ok = gy <= 65535 && gx * 64 * JT_W < (1L << 32) && (!p.in_place || gx * gy == 1);
         done += t;
         // the shares are equal from here on: the rest of a long run is like this one
         if (ok && k == 1000) {
@@ -51,6 +52,11 @@ int main()
     std::vector<int> iters;
     for (int i = 1; i <= 130; ++i) iters.push_back(i);
     for (int i : {255, 256, 257, 1000, 1001, 4095, 4096, 4097, 100001}) iters.push_back(i);
+    // the widest grids (up to 2^40 points)
+    for (int n : {1, 2, 3, 33, 300})
+        for (long m : {1L << 29, 1056964000L, 1056965000L, 1100000000L, (1L << 31) - 1})
+            for (int i : iters)
+                if (jacobi_tiled(n, (int)m) && !check(n, (int)m, i)) return 1;
     for (int n : sides)
         for (int m : sides)
             for (int i : iters)
