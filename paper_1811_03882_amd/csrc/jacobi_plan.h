@@ -36,7 +36,7 @@ inline JacobiPlan jacobi_plan(int n, int m, int iters)
     double cost = 1e300;
     for (int r = 4; r <= 16; r += 4) {
         const int rows = r * JT_W;
-        if (n <= rows && m <= JT_COLS) return JacobiPlan{r, (iters + 4095) / 4096, true};
+        if (n <= rows && m <= JT_COLS) return JacobiPlan{r, (iters - 1) / 4096 + 1, true};
         for (int t = 1; t <= 24 && t <= iters; ++t) {
             const long g = jacobi_groups(n, m, rows, t);
             if (g == 0) break;
@@ -63,7 +63,7 @@ inline JacobiPlan jacobi_plan(int n, int m, int iters)
 // the larger ones first.
 inline int jacobi_share(const JacobiPlan &p, int iters, int done, int k)
 {
-    return (iters - done + (p.launches - k) - 1) / (p.launches - k);
+    return (iters - done - 1) / (p.launches - k) + 1;
 }
 
 }  // namespace dnk

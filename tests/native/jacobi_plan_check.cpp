@@ -51,7 +51,7 @@ int main()
     for (int s : {32, 64, 96, 127, 128, 129, 130, 1000, 1500, 19900, 22100, 24000, 25200, 400000, (1 << 19) - 1}) sides.push_back(s);
     std::vector<int> iters;
     for (int i = 1; i <= 130; ++i) iters.push_back(i);
-    for (int i : {255, 256, 257, 1000, 1001, 4095, 4096, 4097, 100001}) iters.push_back(i);
+    for (int i : {255, 256, 257, 1000, 1001, 4095, 4096, 4097, 100001, INT_MAX - 4095, INT_MAX - 4094, INT_MAX - 1, INT_MAX}) iters.push_back(i);
     // the widest grids (up to 2^40 points)
     for (int n : {1, 2, 3, 33, 300})
         for (long m : {1L << 29, 1056964000L, 1056965000L, 1100000000L, (1L << 31) - 1})
