@@ -732,12 +732,20 @@ static dn_status zero_counters(const Plan &p, char *base, hipStream_t s)
 
 // Does the last op write the caller's NCHW tensor itself?  The first-layer kernel
 // and the pipelined tiles can (one launch and a pass over the result less:
-// 5.9 us of the nine-layer net's 545 at batch 64, 4.1 of 167 at batch 1).
-static bool egress_fused(const dn_net *net, const Plan &p)
+// 5.9 us of the nine-layer net's 545 at batch 64, 4.1 of 167 at batch 1).  Not
+// the first-layer kernel where the caller's buffers share memory: its workgroups
+// still read the image while others write their part of the result.
+static bool egress_fused(const dn_net *net, const Plan &p, const void *x, const void *y)
 {
     const Op &op = p.ops.back();
     if (op.kind != OP_CONV) return false;
-    if (op.first) return true;
+    if (op.first) {
+        const Value &vi = p.vals[0], &vo = p.vals[p.out_val];
+        const char *xb = (const char *)x, *yb = (const char *)y;
+        const size_t xn = (size_t)p.batch * vi.c * vi.h * vi.w * (net->o.input_u8 ? 1 : sizeof(float));
+        const size_t yn = (size_t)p.batch * vo.c * vo.h * vo.w * sizeof(float);
+        return xb + xn <= yb || yb + yn <= xb;
+    }
     return !op.pool && op.tile >= PIPE_TILE && op.tile < PIPE_TILE + PIPE_TILES &&
            op_pipe_ok(net, p.dtype, op, p.batch, net->cw[op.conv].k_pad);
 }
@@ -746,7 +754,7 @@ static dn_status enqueue_resident(const dn_net *net, const Plan &p, char *base, 
 {
     FusedEnds ends;
     ends.zero = p.any_fused && p.ops[0].first && p.cnt_bytes / sizeof(unsigned) < (1u << 31);
-    if (egress_fused(net, p)) ends.nchw = y;
+    if (egress_fused(net, p, x, y)) ends.nchw = y;
     if (p.any_fused && !ends.zero) STCHK(zero_counters(p, base, s));
     const Value &v0 = p.vals[0];
     const float in_inv = p.dtype == FP8 ? 1.0f / net->scale[0] : 1.0f;
@@ -1101,7 +1109,7 @@ static dn_status forward_resident(dn_net *net, void *arena, size_t arena_bytes, 
     // without graphs, or with the cache full (buffers that never repeat), launch
     // eagerly; a forward of one kernel too: launching that costs the host less
     // than replaying a graph of it
-    const bool single = p.ops.size() == 1 && p.ops[0].first && egress_fused(net, p);
+    const bool single = p.ops.size() == 1 && p.ops[0].first && egress_fused(net, p, x, y);
     if (!net->o.use_graph || full || single) return enqueue_resident(net, p, (char *)arena, (const float *)x, (float *)y, s);
     hipGraph_t graph = nullptr;
     HIPCHK(hipStreamBeginCapture(net->cap_stream, hipStreamCaptureModeThreadLocal));
