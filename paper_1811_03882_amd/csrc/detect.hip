@@ -106,15 +106,17 @@ __device__ __forceinline__ Edges edges_of(float4 p)
 // box_iou(p, q) > thresh for the wave's live lanes.  The quotient is needed
 // exactly only where it lies within rounding of the threshold: inter against
 // thresh * uni (relative error below 1e-6) decides every other lane, and the
-// division runs only if some lane is undecided.
-__device__ __forceinline__ bool overlaps(const Edges &p, const Edges &q, float thresh, bool live)
+// division runs only if some lane is undecided.  slack: 1e-30, or infinite (every
+// lane undecided) for thresholds from 0 to 1e-30, to which a quotient too small
+// for a float rounds down.
+__device__ __forceinline__ bool overlaps(const Edges &p, const Edges &q, float thresh, float slack, bool live)
 {
     const float iw = fmaxf(0.0f, fminf(p.r, q.r) - fmaxf(p.l, q.l));
     const float ih = fmaxf(0.0f, fminf(p.d, q.d) - fmaxf(p.t, q.t));
     const float inter = iw * ih;
     const float uni = p.area + q.area - inter;
     const float part = thresh * uni, diff = inter - part;
-    const bool sure = uni > 0.0f && fabsf(diff) > 4e-6f * fabsf(part) + 1e-30f;
+    const bool sure = uni > 0.0f && fabsf(diff) > 4e-6f * fabsf(part) + slack;
     bool over = diff > 0.0f;
     if (__any(live && !sure)) over = (uni > 0.0f ? inter / uni : 0.0f) > thresh;
     return live && over;
@@ -158,6 +160,7 @@ __device__ __forceinline__ void nms_small(const DetectArgs &a, unsigned long lon
         box[q] = q * 64 + lane < m ? sbox[q * 64 + lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         ed[q] = edges_of(box[q]);
     }
+    const float slack = a.nms_thresh >= 0.0f && a.nms_thresh < 1e-30f ? INFINITY : 1e-30f;
 #pragma unroll
     for (int p = 0; p < Q; ++p) {
         for (int i = wave; i < 64 && p * 64 + i < m; i += 4) {
@@ -165,7 +168,7 @@ __device__ __forceinline__ void nms_small(const DetectArgs &a, unsigned long lon
 #pragma unroll
             for (int q = p; q < Q; ++q) {  // only later candidates matter
                 if (q * 64 >= m) break;
-                const unsigned long long over = __ballot(overlaps(e, ed[q], a.nms_thresh, q * 64 + lane < m));
+                const unsigned long long over = __ballot(overlaps(e, ed[q], a.nms_thresh, slack, q * 64 + lane < m));
                 if (lane == 0) rows[(size_t)(p * 64 + i) * Q + q] = over;
             }
         }
