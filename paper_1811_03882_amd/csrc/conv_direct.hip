@@ -1160,7 +1160,7 @@ bool halo2_ok(int dt, const ConvArgs &a, bool as_four)
 static int halo2_fix(int dt, const ConvArgs &a)
 {
     const bool fix = dt == BF16 && a.R == 3 && a.S == 3 && a.stride == 1 &&
-                     (size_t)(a.H + 64) * a.W * a.cin_p * esize(dt) < (1u << 30);
+                     (size_t)(a.H + a.pad + 64) * a.W * a.cin_p * esize(dt) < (1u << 30);
     return fix && (a.cin_p == 16 || a.cin_p == 32) ? a.cin_p / seg_el(BF16) : 0;
 }
 
@@ -1189,8 +1189,8 @@ static hipError_t go_halo2(const ConvArgs &a, int grid, int nbuf, size_t lds, hi
 }
 
 // BF16 3x3 stride-1 layers of 16 and 32 channels, the shapes in use, run the
-// instances with the window's layout built in (images below 1 GB: their
-// transfers mark dead slots by an offset past that).  The general form issues
+// instances with the window's layout built in (images below 1 GB, padding below
+// them included: their transfers mark dead slots by an offset past that).  The general form issues
 // 535 vector instructions a wave and tile besides the MFMAs, more than the
 // MFMAs take: tile positions divided out (150), window addresses (84), fragment
 // addresses (72).  64 images of 104 x 104 x 32 -> 64 channels, pooled: 38.5 us
