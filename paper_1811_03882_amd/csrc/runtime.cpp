@@ -2073,6 +2073,39 @@ extern "C" dn_status dn_time_layer(dn_net *net, int layer, int batch, int h, int
 
 // ---------------------------------------------------------------- standalone layers
 
+// Is the persistent halo kernel the choice for a conv on its own?  It reads
+// every input pixel once and keeps the weights in registers (BF16 + pool,
+// 104x104x32 -> 64, batch 64: 69 us on a GEMM tile, 28 here), but a call pays for
+// those weights, and its tiles of 16 (8 with four 16-channel blocks) x 32 pixels
+// fill the chip later than a GEMM's.  The lines lie where it stops losing to the
+// GEMM tiles; measured over 1 to 3584 tiles (104x104 at batches 1 to 64, 1x1 to
+// 3x3, 8 to 64 channels), times in us, GEMM tile against this kernel:
+//   * BF16 3x3 of 16 or 32 channels, the built-in window: always with up to two
+//     blocks (16 -> 16 on one tile 1.4 to 1.7 times faster), with four from a
+//     tile a CU on (260 tiles: 1.01 to 1.2 times; 52: slower).
+//   * The general form, up to two blocks: 3x3 in 16 and 8 bits at any number (FP8
+//     32 -> 32, 28 tiles: 1.0 times, pooled 1.1; 448: 1.5); else from about a tile
+//     a CU on, a little earlier with one block (FP8 1x1 8 -> 16, 112 tiles: 0.93
+//     times, 224: 1.05; 32 -> 32, 224: 0.98, 448: 1.44).
+//   * The general form, four blocks: from 2.5 tiles a CU on (FP8 3x3 32 -> 64, 624
+//     tiles: 0.99 times; 676: 1.07), pooled from two (FP8: 468 1.04, 520 1.16).  FP32,
+//     whose matrix rate leaves less to save, from 4.5 on (3x3 16 -> 64, 1040
+//     tiles: 0.98, 1248: 1.07), with a single K step from two on (520: 1.04).
+//     Not 1x1 convs that the pipelined tiles take: nothing is read twice there
+//     (BF16 64 -> 64, 468 tiles: 1.2 times on a pipelined tile; 520 here: 0.9).
+static bool prefer_halo2(int dt, const ConvArgs &g)
+{
+    if (!halo2_ok(dt, g, true)) return false;
+    bool fixed;
+    const long tiles = halo2_tiles(dt, g, &fixed);
+    const bool four = g.cout_p > 32 || !halo2_ok(dt, g);
+    if (fixed) return !four || tiles >= 256;
+    if (!four) return (g.R * g.S >= 9 && dt != F32) || tiles >= (g.cout_p <= 16 ? 224 : 256);
+    if (g.R * g.S == 1 && pipe_ok(dt, g)) return false;
+    if (dt == F32) return tiles >= (g.R * g.S * g.cin_p <= 16 ? 512 : 1152);
+    return tiles >= (g.pool ? 512 : 640);
+}
+
 static dn_status conv_geometry(const dn_conv_desc *d, ConvArgs *a, int *tile, int *splits, size_t *wbytes,
                                size_t *vbytes, size_t *wsbytes)
 {
@@ -2110,22 +2143,11 @@ static dn_status conv_geometry(const dn_conv_desc *d, ConvArgs *a, int *tile, in
         ConvArgs g{};
         g.batch = d->batch; g.H = d->in_h; g.W = d->in_w; g.Ho = Ho; g.Wo = Wo;
         g.R = g.S = d->ksize; g.stride = d->stride; g.pad = d->pad; g.cin_p = cin_p; g.cout_p = cout_p; g.k_pad = k_pad;
-        // The persistent halo kernel for small K reads every input pixel once
-        // (BF16 + pool: 104x104x32 -> 64, batch 64: 69 us on a GEMM tile, 28
-        // here; 100x100x32 -> 48, batch 34: 36 us, 17 here).  Its tiles for
-        // four channel blocks lose where they leave CUs without one (56x56x32
-        // -> 64, batch 4, 56 tiles: 7.3 us on a GEMM tile, 7.6 here), and in
-        // the general form, which 24 channels take, below two a CU (80x80,
-        // batch 12, 360 tiles: 11.1 and 11.2; 1768 tiles: 33 and 22).
-        bool halo = sp <= 0 && halo2_ok(dt, g, true);
-        if (halo && dt == BF16 && (cout_p > 32 || !halo2_ok(dt, g))) {
-            bool fixed;
-            halo = halo2_tiles(dt, g, &fixed) >= (fixed ? 256 : 512);
-        }
+        g.pool = d->pool ? 1 : 0;
         // one or two K-tiles on less than a tile a CU: no pipeline to fill
         // (8x8x128 -> 256 1x1, batch 12: 7.5 us register-staged, 7.75 pipelined)
         const bool brief = nkt <= 2 && (long)((M + 63) / 64) * ((cout_p + 63) / 64) < 256;
-        if (halo) {
+        if (sp <= 0 && prefer_halo2(dt, g)) {
             t = HALO2_TILE;
         } else if (!brief && pipe_ok(dt, g)) {
             // here a split costs a second launch (the workspace has no zeroed
