@@ -262,14 +262,18 @@ static const PipeCost kPipeCost[PIPE_TILES] = {
 static bool finish_in_kernel(int tile, int splits);
 
 // Microseconds the pipelined tile is expected to take; in_net: split convs may
-// finish in the GEMM launch.
-static float pipe_time(int dt, int i, int M, int N, int nkt, int splits, bool in_net)
+// finish in the GEMM launch.  Otherwise the finish is a launch of its own, in
+// which a thread reads its outputs' partials one split after the other, four
+// times as many where a pool is fused: about 0.31 us each, of which the launch
+// hides the first four (BF16 8x8x128 -> 64, 3x3, at 2 / 4 / 8 / 16 splits: 7.5,
+// 7.5, 8.3, 10.7 us, pooled 9.9, 11.7, 16.5, 26.5).
+static float pipe_time(int dt, int i, int M, int N, int nkt, int splits, bool in_net, bool pool)
 {
     const int CUS = 256;
     const TileCfg t = tile_cfg(PIPE_TILE + i);
     PipeCost c = kPipeCost[i];
     if (dt == F32) {
-        c.cost = (float)t.bm * t.bn / 256.0f * 64.0f / 2100.0f / 1.0f;
+        c.cost = (float)t.bm * t.bn / 256.0f * 64.0f / 2100.0f;
         c.alone = std::max(c.alone, c.cost);
     }
     if (dt == FP8 && i == PIPE_TILES - 1) c = {0.95f, 0.95f, 4.0f, 1};  // more registers per wave
@@ -284,17 +288,18 @@ static float pipe_time(int dt, int i, int M, int N, int nkt, int splits, bool in
     if (rest > 0) us += kt * std::max((double)c.alone, c.cost * rest) + c.round;
     if (splits > 1) {
         const double mb = 2.0 * splits * M * N * 4.0 / 1e6;
-        us += in_net && finish_in_kernel(PIPE_TILE + i, splits) ? 2.0 + mb / 3.0 : 5.0 + mb / 3.0;
+        if (in_net) us += finish_in_kernel(PIPE_TILE + i, splits) ? 2.0 + mb / 3.0 : 5.0 + mb / 3.0;
+        else us += 5.0 + 0.31 * std::max(0, splits * (pool ? 4 : 1) - 4) + mb / 3.0;
     }
     return (float)us;
 }
 
-static int pipe_tile(int dt, int M, int N, int nkt, int splits, bool in_net, float *us = nullptr)
+static int pipe_tile(int dt, int M, int N, int nkt, int splits, bool in_net, bool pool, float *us = nullptr)
 {
     int best = 0;
     float bt = 1e30f;
     for (int i = 0; i < PIPE_TILES; ++i) {
-        const float v = pipe_time(dt, i, M, N, nkt, splits, in_net);
+        const float v = pipe_time(dt, i, M, N, nkt, splits, in_net, pool);
         if (v < bt) { bt = v; best = i; }
     }
     if (us) *us = bt;
@@ -595,7 +600,7 @@ static dn_status make_plan(const dn_net *net, int dtype, int mode, int batch, in
             heuristic_tile(M, op.cout_p, k_pad / bk_el(dtype), &op.tile, &op.splits);
             if (halo) op.splits = 1;
             if (op_pipe_ok(net, dtype, op, batch, k_pad))
-                op.tile = pipe_tile(dtype, M, op.cout_p, k_pad / bk_el(dtype), op.splits, true);
+                op.tile = pipe_tile(dtype, M, op.cout_p, k_pad / bk_el(dtype), op.splits, true, op.pool);
             else if (halo)
                 op.tile = HALO_TILE;
         }
@@ -607,7 +612,7 @@ static dn_status make_plan(const dn_net *net, int dtype, int mode, int batch, in
                 heuristic_tile(M, op.cout_p, k_pad / bk_el(dtype), &op.tile, &unused);  // 16x16-block tiles
             }
             if (!tuned && !is_halo(op.tile) && op_pipe_ok(net, dtype, op, batch, k_pad))
-                op.tile = pipe_tile(dtype, M, op.cout_p, k_pad / bk_el(dtype), op.splits, true);
+                op.tile = pipe_tile(dtype, M, op.cout_p, k_pad / bk_el(dtype), op.splits, true, op.pool);
         }
         op.ws_bytes = op.splits > 1 ? align256((size_t)op.splits * M * op.cout_p * 4) : 0;
         ws = std::max(ws, op.ws_bytes);
@@ -2156,11 +2161,11 @@ static dn_status conv_geometry(const dn_conv_desc *d, ConvArgs *a, int *tile, in
                 float best = 1e30f;
                 for (int s = 1; s <= 16 && s <= nkt; s *= 2) {
                     float us;
-                    pipe_tile(dt, M, cout_p, nkt, s, false, &us);
+                    pipe_tile(dt, M, cout_p, nkt, s, false, g.pool, &us);
                     if (us < best) { best = us; sp = s; }
                 }
             }
-            t = pipe_tile(dt, M, cout_p, nkt, sp, false);
+            t = pipe_tile(dt, M, cout_p, nkt, sp, false, g.pool);
         }
     }
     if (t < 0) t = ht;
@@ -2372,7 +2377,7 @@ static dn_status bwd_plan_tile(const dn_conv_desc *f, int accumulate, int *tile,
     const int nkt = a.k_pad / bk_el(f->dtype);
     heuristic_tile(a.M, a.cout_p, nkt, tile, splits);
     if (halo_ok(f->dtype, a)) *splits = 1;
-    if (pipe_ok(f->dtype, a)) *tile = pipe_tile(f->dtype, a.M, a.cout_p, nkt, *splits, false);
+    if (pipe_ok(f->dtype, a)) *tile = pipe_tile(f->dtype, a.M, a.cout_p, nkt, *splits, false, false);
     return DN_OK;
 }
 
