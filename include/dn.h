@@ -518,7 +518,9 @@ dn_status dn_mfma_peak(int dtype, int device, double *tflops);
 
 /* Number of compiled conv tile configurations and their shapes: output tile
  * bm x bn, waves_m x waves_n waves, and the side of the MFMA blocks a BF16
- * conv uses with it (16 or 32; other dtypes always use 16x16 blocks).  Tiles
+ * conv uses with it (16 or 32; other dtypes always use 16x16 blocks).  The
+ * 256x256 tile of the table's last ten is one for F32 and BF16: an FP8 conv given
+ * its number runs the 192x256 tile after it.  Tiles
  * with the same block side give bitwise-identical results; 16 and 32 differ
  * by FP32 summation order only.  Any out-pointer may be NULL; a tile outside
  * [0, dn_tile_count()) is DN_EINVAL. */

@@ -427,8 +427,7 @@ static hipError_t go_pipe(ConvArgs a, hipStream_t s)
 template <int DT> static hipError_t dispatch_pipe(int i, const ConvArgs &a, hipStream_t s)
 {
     switch (i) {
-    // (FP8's 32-byte fragments of a 128x64 wave tile do not fit in the registers)
-    case 0: if constexpr (DT != FP8) return go_pipe<DT, 256, 256, 2, 4, 2, 2>(a, s); else return go_pipe<DT, 192, 256, 2, 4, 2, 2>(a, s);
+    case 0: if constexpr (pipe_own(DT, 0)) return go_pipe<DT, 256, 256, 2, 4, 2, 2>(a, s); else return go_pipe<DT, 192, 256, 2, 4, 2, 2>(a, s);
     case 1: return go_pipe<DT, 192, 256, 2, 4, 2, 2>(a, s);
     case 2: return go_pipe<DT, 128, 128, 2, 4, 2, 4>(a, s);
     case 3: return go_pipe<DT, 96, 128, 2, 2, 2, 2>(a, s);

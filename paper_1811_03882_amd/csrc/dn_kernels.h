@@ -121,6 +121,10 @@ hipError_t launch_conv_halo2(int dt, const ConvArgs &a, hipStream_t s);
 // The pipelined GEMM kernel (conv_pipe.hip): tiles PIPE_TILE .. + PIPE_TILES - 1
 // of the table, for convs that pipe_ok().
 constexpr int PIPE_TILE = 48, PIPE_TILES = 10;
+// Is tile PIPE_TILE + i a kernel of its own?  FP8 has no 256x256 one: its 32-byte
+// fragments of a 128x64 wave tile do not fit in the registers, and the number
+// runs the 192x256 tile's.
+constexpr bool pipe_own(int dt, int i) { return dt != FP8 || i != 0; }
 bool pipe_ok(int dt, const ConvArgs &a);
 hipError_t launch_conv_pipe(int dt, int i, const ConvArgs &a, hipStream_t s);
 

@@ -299,6 +299,7 @@ static int pipe_tile(int dt, int M, int N, int nkt, int splits, bool in_net, boo
     int best = 0;
     float bt = 1e30f;
     for (int i = 0; i < PIPE_TILES; ++i) {
+        if (!pipe_own(dt, i)) continue;
         const float v = pipe_time(dt, i, M, N, nkt, splits, in_net, pool);
         if (v < bt) { bt = v; best = i; }
     }
@@ -1734,8 +1735,9 @@ static void pick_tuned(const std::vector<std::tuple<float, int, int>> &timed, in
     }
 }
 
-static bool tile_fits(int tile, int cout_p)
+static bool tile_fits(int dt, int tile, int cout_p)
 {
+    if (tile >= PIPE_TILE && !pipe_own(dt, tile - PIPE_TILE)) return false;  // another number's kernel
     const TileCfg t = tile_cfg(tile);
     // avoid tiles whose N extent is more than 4x the layer width (pure waste)
     return t.bn <= std::max(16, cout_p) * 4 && t.bn <= std::max(cout_p, 16) * 2;
@@ -1784,7 +1786,7 @@ extern "C" dn_status dn_autotune(dn_net *net, int batch, int h, int w, void *str
         if (op_halo2_ok(net, p.dtype, op, net->cw[op.conv].k_pad)) cands.push_back(HALO2_TILE);
         const bool pipe = op_pipe_ok(net, p.dtype, op, batch, net->cw[op.conv].k_pad);
         for (int t = 0; t < (pipe ? tile_count() : PIPE_TILE); ++t)
-            if (tile_fits(t, op.cout_p)) cands.push_back(t);
+            if (tile_fits(p.dtype, t, op.cout_p)) cands.push_back(t);
         for (int t : cands) {
             if (rc != DN_OK) break;
             const TileCfg tc = is_halo(t) ? TileCfg{1 << 30, 1 << 30, 1, 1} : tile_cfg(t);
@@ -2909,7 +2911,7 @@ static dn_status autotune_backward(dn_net *net, int layer, int batch, int h, int
         if (op_halo2_ok(net, dt, op, net->cw[op.conv].k_pad)) cands.push_back(HALO2_TILE);
         const bool pipe = op_pipe_ok(net, dt, op, batch, net->cw[op.conv].k_pad);
         for (int t = 0; t < (pipe ? tile_count() : PIPE_TILE); ++t)
-            if (tile_fits(t, op.cout_p)) cands.push_back(t);
+            if (tile_fits(dt, t, op.cout_p)) cands.push_back(t);
         std::vector<std::tuple<float, int, int>> timed;
         for (int t : cands) {
             const TileCfg tc = is_halo(t) ? TileCfg{1 << 30, 1 << 30, 1, 1} : tile_cfg(t);
@@ -2949,7 +2951,7 @@ static dn_status autotune_backward(dn_net *net, int layer, int batch, int h, int
         if (halo_ok(dt, a)) cands.push_back(HALO_TILE);
         if (halo2_ok(dt, a)) cands.push_back(HALO2_TILE);
         for (int t = 0; t < (pipe_ok(dt, a) ? tile_count() : PIPE_TILE); ++t)
-            if (tile_fits(t, a.cout_p)) cands.push_back(t);
+            if (tile_fits(dt, t, a.cout_p)) cands.push_back(t);
         std::vector<std::tuple<float, int, int>> timed;
         for (int t : cands) {
             const TileCfg tc = is_halo(t) ? TileCfg{1 << 30, 1 << 30, 1, 1} : tile_cfg(t);
