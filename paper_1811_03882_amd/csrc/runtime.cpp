@@ -278,12 +278,12 @@ static float pipe_time(int dt, int i, int M, int N, int nkt, int splits, bool in
     }
     if (dt == FP8 && i == PIPE_TILES - 1) c = {0.95f, 0.95f, 4.0f, 1};  // more registers per wave
     const float kt = (float)((nkt + splits - 1) / splits);
-    const double wgs = (double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
+    const long wgs = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
     // workgroups of the busiest CU: whole ones while few, the mean once
-    // enough rounds even out
-    const double mean = wgs / CUS;
-    const double n = mean > 3.0 * c.per_cu ? mean : std::ceil(mean);
-    const double full = std::floor(n / c.per_cu), rest = n - full * c.per_cu;
+    // enough rounds even out (truncation is the floor here, without a library call:
+    // standalone convs price up to 50 choices a call)
+    const double n = wgs > 3l * c.per_cu * CUS ? (double)wgs / CUS : (double)((wgs + CUS - 1) / CUS);
+    const double full = (double)(long)(n / c.per_cu), rest = n - full * c.per_cu;
     double us = full * (kt * std::max(c.alone, c.cost * c.per_cu) + c.round);
     if (rest > 0) us += kt * std::max((double)c.alone, c.cost * rest) + c.round;
     if (splits > 1) {
@@ -2328,7 +2328,7 @@ extern "C" dn_status dn_egress(int dtype, int batch, int c, int h, int w, const 
 // (spread, when f is strided) output gradient: in_c = f.cout, cout = f.in_c,
 // stride 1, pad k-1-pad, linear, bias 0.  hz x wz is its input size.
 static dn_status bwd_desc(const dn_conv_desc *f, int accumulate, dn_conv_desc *b, int *ho, int *wo, int *hz, int *wz,
-                          int tile = -1, int splits = 0)
+                          int tile = -1, int splits = 0, ConvArgs *geom = nullptr)
 {
     if (!f) return fail(DN_EINVAL, "conv desc is NULL");
     if (f->dtype != DN_F32 && f->dtype != DN_BF16) return fail(DN_EUNSUPPORTED, "backward: F32 and BF16 only");
@@ -2348,9 +2348,11 @@ static dn_status bwd_desc(const dn_conv_desc *f, int accumulate, dn_conv_desc *b
     b->cout = f->in_c; b->ksize = f->ksize; b->stride = 1; b->pad = f->ksize - 1 - f->pad;
     b->activation = DN_ACT_LINEAR; b->dtype = f->dtype; b->residual = accumulate ? 1 : 0;
     b->in_scale = b->res_scale = b->out_scale = 1.0f;
-    b->tile = -1; b->splits = 0;
+    b->tile = 0; b->splits = 1;  // for its geometry, without evaluating the rules
     ConvArgs a;
     STCHK(conv_geometry(b, &a, nullptr, nullptr, nullptr, nullptr, nullptr));
+    b->tile = -1; b->splits = 0;
+    if (geom) *geom = a;
     if (tile >= 0) {  // an explicit (tuned) choice
         if (tile == HALO_TILE && !halo_ok(f->dtype, a)) return fail(DN_EUNSUPPORTED, "backward: halo tile does not fit");
         if (tile == HALO2_TILE && !halo2_ok(f->dtype, a)) return fail(DN_EUNSUPPORTED, "backward: halo tile does not fit");
@@ -2370,9 +2372,8 @@ static dn_status bwd_plan_tile(const dn_conv_desc *f, int accumulate, int *tile,
 {
     dn_conv_desc b;
     int ho, wo, hz, wz;
-    STCHK(bwd_desc(f, accumulate, &b, &ho, &wo, &hz, &wz));
     ConvArgs a;
-    STCHK(conv_geometry(&b, &a, nullptr, nullptr, nullptr, nullptr, nullptr));
+    STCHK(bwd_desc(f, accumulate, &b, &ho, &wo, &hz, &wz, -1, 0, &a));
     *tile = b.tile;
     *splits = 1;
     if (is_halo(b.tile)) return DN_OK;
@@ -2393,10 +2394,12 @@ static std::string bwd_sig(const dn_conv_desc *f, int accumulate)
 }
 
 // Scratch of a backward-data conv: split-K partials, then the spread gradient.
-static dn_status bwd_scratch(const dn_conv_desc *f, const dn_conv_desc *b, int hz, int wz, size_t *ws, size_t *z)
+// a, tile, splits (may be NULL): the conv's arguments and choice, from the same pass.
+static dn_status bwd_scratch(const dn_conv_desc *f, const dn_conv_desc *b, int hz, int wz, size_t *ws, size_t *z,
+                             ConvArgs *a = nullptr, int *tile = nullptr, int *splits = nullptr)
 {
     size_t need = 0;
-    STCHK(conv_geometry(b, nullptr, nullptr, nullptr, nullptr, nullptr, &need));
+    STCHK(conv_geometry(b, a, tile, splits, nullptr, nullptr, &need));
     *ws = align256(need);
     *z = f->stride > 1 ? align256((size_t)f->batch * hz * wz * cpad(f->dtype, f->cout) * esize(f->dtype)) : 0;
     return DN_OK;
@@ -2460,8 +2463,10 @@ static dn_status enqueue_conv_backward(const dn_conv_desc *f, const void *dy, co
     dn_conv_desc b;
     int ho, wo, hz, wz;
     STCHK(bwd_desc(f, accumulate, &b, &ho, &wo, &hz, &wz, tile, splits));
+    ConvArgs a;
+    int use_tile = 0, use_splits = 1;
     size_t ws = 0, z = 0;
-    STCHK(bwd_scratch(f, &b, hz, wz, &ws, &z));
+    STCHK(bwd_scratch(f, &b, hz, wz, &ws, &z, &a, &use_tile, &use_splits));
     if (ws + z > 0 && (!scratch || scratch_bytes < ws + z))
         return fail(DN_EINVAL, "conv backward: needs %zu workspace bytes (%zu given)", ws + z, scratch_bytes);
     const void *src = dy;
@@ -2470,9 +2475,6 @@ static dn_status enqueue_conv_backward(const dn_conv_desc *f, const void *dy, co
         HIPCHK(launch_dilate(f->dtype, dy, zb, f->batch, ho, wo, cpad(f->dtype, f->cout), hz, wz, f->stride, s));
         src = zb;
     }
-    ConvArgs a;
-    int use_tile = 0, use_splits = 1;
-    STCHK(conv_geometry(&b, &a, &use_tile, &use_splits, nullptr, nullptr, nullptr));
     a.x = src; a.w = w_packed; a.bias = zero_bias; a.wscale = unit_scale;
     a.res = accumulate ? dx : nullptr;
     a.y = dx;
