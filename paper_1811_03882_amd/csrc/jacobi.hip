@@ -74,8 +74,8 @@ __global__ void jacobi_zero(unsigned long long *p) { *p = 0ull; }
 //   * Every value is formed by the same four operations in the same order as in
 //     jacobi_step, so the result has the same bits for any R, t and tiling.
 // Bound by instruction issue and the launches.  Measured, 64 iterations of
-// 1000x1500: 491 us one launch per iteration, 106 us as
-// four launches of 16 on 96-row patches.
+// 1000x1500: 491 us one launch per iteration, 92 us as four launches of 16 on
+// 96-row patches.
 
 template <int CTRL> __device__ __forceinline__ double wave_shift(double v)
 {
@@ -186,8 +186,18 @@ __global__ void __launch_bounds__(64 * JT_W, 2) jacobi_tile(const double *u, dou
         if (w.out1) q[1] = c[r][1];
     }
     if (max_change) {
+        // one atomic per workgroup: they queue up at the one address, about 10 ns
+        // each.  One per wave made flat grids, which have more waves here than on
+        // the kernel of one iteration, slower than on that kernel (3 x 1000000, 16
+        // iterations: 899 us against 869; 195 with one per workgroup)
+        __shared__ double most[JT_W];
         for (int off = 32; off > 0; off >>= 1) ch = fmax(ch, __shfl_xor(ch, off));
-        if (w.lane == 0) atomicMax(max_change, (unsigned long long)__double_as_longlong(ch));
+        if (w.lane == 0) most[w.wave] = ch;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int k = 1; k < JT_W; ++k) ch = fmax(ch, most[k]);
+            if (ch > 0.0) atomicMax(max_change, (unsigned long long)__double_as_longlong(ch));
+        }
     }
 }
 
