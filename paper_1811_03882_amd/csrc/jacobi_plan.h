@@ -23,11 +23,13 @@ constexpr int JT_MAX_Y = 65535, JT_MAX_X = (1 << 23) - 1;
 inline bool jacobi_tiled(int n, int m) { return n < (1 << 19) && m <= (JT_COLS - 2) * JT_MAX_X; }
 
 // Rows per wave and launches for `iters` iterations: the least launches x
-// (launch + t x iteration) over patch heights and iterations per launch t.  A
-// launch costs about 6.5 us with its loads and stores; an iteration 0.15 us of
-// barrier and LDS latency and, per workgroup a CU runs at once, 96 clocks of
-// issue a row (two waves on each SIMD, 12 instructions for two columns).  At
-// 1000x1500 the rule takes 96-row patches and 16 iterations: 256 workgroups.
+// (launch + t x iteration) over patch heights and iterations per launch t.  The
+// model ranks the choices: 6.5 us a launch with its loads and stores; an iteration
+// 0.15 us of barrier and LDS latency and, per workgroup a CU runs at once, 96
+// clocks of issue a row (two waves on each SIMD, 12 instructions for two columns).
+// It leaves out what patches at the grid's edge do more, for which a launch waits:
+// 1000x1500 at 64 iterations takes 92 us where it says 71, on the plan it
+// chooses, 96-row patches and 16 iterations (256 workgroups).
 // A grid that fits in one patch needs no rim and no partner buffer: one launch,
 // in place (at most 4096 iterations each, so that a launch stays short).
 inline JacobiPlan jacobi_plan(int n, int m, int iters)

@@ -240,11 +240,15 @@ static void heuristic_tile(int M, int N, int K, int *tile, int *splits)
 // `nkt` K-tiles in all and `splits` of them side by side.  A CU's time per
 // K-tile is about cost x (workgroups it runs), but never less than what one
 // workgroup takes alone (alone), which barriers and LDS latency set; each
-// round adds its prologue and epilogue (round).  cost / alone / round: fitted
-// to BF16 timings on MI355X (microseconds per K-tile: 13x13x1024 -> 1024 and
-// 13x13x512 -> 1024 at batch 64 and 16, 16x16x256 -> 512 at batch 16,
-// 52x52x64 -> 128 and its gradient); FP8 measured within 10 % of the same
-// figures.  FP32 is bound by its matrix rate: 64 values per clock and SIMD.
+// round adds its prologue and epilogue (round).  The figures (microseconds; BF16,
+// FP8 takes the same ones) rank the tiles, they do not predict a time: they stem
+// from an earlier form of the kernel and overstate this one (13x13x1024 -> 1024 at
+// batch 64 on 192x256: 182 us by the rule, 150 measured; a 64x64 tile alone takes
+// 0.2 to 0.26 us a K-tile where the weights stay in an XCD's L2).  Timed over 500
+// shapes (M 16 to 60000, 16 to 1024 channels out, 1x1 and 3x3), the tile they take
+// needs 1.05 (BF16), 1.08 (FP8), 1.01 (FP32) times the best one's time at the same
+// split count, tile and split together 1.07, 1.10, 1.02.  FP32 is bound by its
+// matrix rate: 64 values per clock and SIMD.
 struct PipeCost { float cost, alone, round; int per_cu; };
 static const PipeCost kPipeCost[PIPE_TILES] = {
     {1.33f, 1.33f, 6.0f, 1},   // 256x256
@@ -639,7 +643,6 @@ static dn_status make_plan(const dn_net *net, int dtype, int mode, int batch, in
 
 // ---------------------------------------------------------------- enqueue
 
-// x8 set: the image is 8-bit pixels (value q / 255) instead of FP32 x.
 // Where a forward's result and its split-K counters go when a conv kernel takes
 // over the egress or the clearing of the counters.
 struct FusedEnds {
@@ -647,6 +650,7 @@ struct FusedEnds {
     bool zero = false;        // the first-layer kernel clears the plan's counters
 };
 
+// x8 set: the image is 8-bit pixels (value q / 255) instead of FP32 x.
 static dn_status enqueue_first(const dn_net *net, const Plan &p, const Op &op, const float *x, char *base,
                                hipStream_t s, bool use32, const unsigned char *x8 = nullptr,
                                const FusedEnds &ends = FusedEnds())
@@ -2326,7 +2330,10 @@ extern "C" dn_status dn_egress(int dtype, int batch, int c, int h, int w, const 
 
 // The backward-data conv of forward conv `f`, as a forward conv over the
 // (spread, when f is strided) output gradient: in_c = f.cout, cout = f.in_c,
-// stride 1, pad k-1-pad, linear, bias 0.  hz x wz is its input size.
+// stride 1, pad k-1-pad, linear, bias 0.  hz x wz is its input size.  tile -1
+// leaves GEMM tile and split to conv_geometry()'s rule: the standalone entry
+// point, and bwd_plan_tile() for the halo kernels alone.  geom (may be NULL): the
+// conv's geometry, without a choice.
 static dn_status bwd_desc(const dn_conv_desc *f, int accumulate, dn_conv_desc *b, int *ho, int *wo, int *hz, int *wz,
                           int tile = -1, int splits = 0, ConvArgs *geom = nullptr)
 {
@@ -2526,7 +2533,7 @@ struct BwdPlan {
     std::vector<dn_conv_desc> fwd;   // per op: the forward conv as a standalone desc (convs only)
     std::vector<char> pool_leaky;    // per op: this pool applies the leaky gradient of its input's producer
     std::vector<char> acc;           // per op: its input's gradient already holds a contribution (add, not write)
-    std::vector<std::pair<int, int>> btile;  // per conv op: backward (tile, splits); (-1, 0) = heuristic
+    std::vector<std::pair<int, int>> btile;  // per conv op: backward (tile, splits), tuned or bwd_plan_tile()'s
     size_t bws_off = 0, bws_bytes = 0;  // backward conv scratch
     size_t gin_off = 0, mabs_off = 0;   // NCHW FP32 input gradient, per-image mean |g|
     size_t total = 0;
